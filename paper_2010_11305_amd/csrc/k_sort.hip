@@ -909,7 +909,9 @@ struct TabCursor {
 template <typename F>
 __device__ __forceinline__ int64_t walk_starts(const Dev& dv, const uint32_t* __restrict__ sk, int64_t n,
                                                int64_t i0, const uint32_t (&k)[kUqPer], F&& on_start) {
-  uint32_t prev = i0 > 0 ? sk[i0 - 1] : kKeyInvalid;
+  // a thread of the last tile past the keys has no predecessor either: what lies there is
+  // no key, and the cursor below would walk off the key bases looking for its table
+  uint32_t prev = i0 > 0 && i0 < n ? sk[i0 - 1] : kKeyInvalid;
   TabCursor cur;
   int pt = -1;        // table of prev (valid prev only)
   uint32_t pset = 0;  // set of prev (cached table only)
