@@ -581,6 +581,8 @@ __device__ __forceinline__ int32_t probe_set(const int32_t* __restrict__ tg, int
   return found;
 }
 
+// MAXA bounds assoc at compile time (a kernel of few ways then needs no registers for 64).
+template <int MAXA = 64>
 __device__ __forceinline__ int32_t probe_slot(const Dev& dv, const TableDesc& td, int32_t r) {
   if (td.n_sets == 0) return -1;
   const int64_t set = (int64_t)mod_by((uint32_t)r, td.by_sets);
@@ -593,8 +595,9 @@ __device__ __forceinline__ int32_t probe_slot(const Dev& dv, const TableDesc& td
     case 4: w = probe_set<4>(tg, r); break;
     case 8: w = probe_set<8>(tg, r); break;
     case 16: w = probe_set<16>(tg, r); break;
-    case 32: w = probe_set<32>(tg, r); break;
-    default: w = probe_set<64>(tg, r); break;
+    default:
+      if constexpr (MAXA > 16) w = dv.assoc == 32 ? probe_set<32>(tg, r) : probe_set<64>(tg, r);
+      break;
   }
   return w >= 0 ? (int32_t)(base + w) : -1;
 }
@@ -649,6 +652,19 @@ __device__ __forceinline__ void part_range(int64_t a, int64_t b, int part, int p
   const int64_t n = b - a;
   lo = a + n * part / parts;
   hi = a + n * (part + 1) / parts;
+}
+
+// The workgroup's copy of table t's statistics.
+__device__ __forceinline__ unsigned long long* stat_of(const Dev& dv, int t) {
+  const int copy = (int)blockIdx.x & ((1 << dv.stat_shift) - 1);
+  return dv.stats + (((int64_t)t << dv.stat_shift) + copy) * kStatStride;
+}
+
+// Zeroes fields [f0, f1] of every copy of every table's statistics, by the whole grid.
+__device__ __forceinline__ void zero_stats(const Dev& dv, int f0, int f1) {
+  const int64_t n = (int64_t)dv.T << dv.stat_shift, stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
+    for (int f = f0; f <= f1; ++f) dv.stats[i * kStatStride + f] = 0;
 }
 
 __device__ __forceinline__ uint64_t lanemask_lt() {

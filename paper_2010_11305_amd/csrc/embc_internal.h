@@ -17,7 +17,7 @@
 //                                   slot (it moves between record and slot with the row); absent
 //                                   under SGD
 //   cnt   [total_rows] int32        LFU: access counts; absent under LRU
-//   desc  [T] TableDesc, key_base [T+1], stats [T][kNStat] u64, err flags
+//   desc  [T] TableDesc, key_base [T+1], stats [T][copies][kStatStride] u64, err flags
 // Rows of all tables are concatenated (global row = row_base[t] + row), and so
 // are cache slots, so one base pointer serves every table.
 #pragma once
@@ -46,6 +46,20 @@ enum : int {
   kStLookups = 0, kStHitLookups, kStBwdLookups, kStUnique, kStUniqueHits, kStInserts, kStBypasses,
   kStEvictions, kStEmptyFills, kStHitEvictions, kStInvalidFwd, kStInvalidBwd, kNStat
 };
+
+// Each table's statistics are kept in several copies, one 128-byte line each; a workgroup
+// adds to the copy of its index and a reader sums them.  Atomic additions to one address
+// from all XCDs complete one after another, and a kernel's waves all end with some:
+// with one copy and one addition per wave or row group they were half of the forward probe
+// at 0.5M lookups (45 us) and most of the replacement decisions of one table (430 us).
+constexpr int kStatStride = 16;
+constexpr int kMaxStatShift = 5;
+// Few tables want many copies; many tables spread their additions by themselves.
+constexpr int stat_shift_for(int64_t T) {
+  int s = kMaxStatShift;
+  while (s > 0 && (T << s) > 4096) --s;
+  return s;
+}
 
 enum : int { kErrIndex = 1, kErrOffsets = 2, kErrSort = 4 };
 constexpr int kMaxPasses = 4;  // 8-bit digits of a 32-bit sort key
@@ -87,7 +101,7 @@ struct Dev {
   float* acc_rows;    // nullptr when the accumulators of uncached rows are in the records
   const TableDesc* desc;
   const int64_t* key_base;       // [T+1], key_base[T] = total key space
-  unsigned long long* stats;     // [T][kNStat]
+  unsigned long long* stats;     // [T][1 << stat_shift][kStatStride], see stat_of
   int32_t* err;
   int32_t T;
   int32_t dim;
@@ -99,6 +113,7 @@ struct Dev {
   int32_t policy;     // 0 LRU, 1 LFU
   int32_t rounding;   // 0 nearest, 1 stochastic
   int32_t optimizer;  // 0 SGD, 1 row-wise Adagrad
+  int32_t stat_shift; // log2 of the copies of each table's statistics
   float lr;
   float eps;
   uint64_t seed;

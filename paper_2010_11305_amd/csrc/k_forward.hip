@@ -30,7 +30,8 @@ hipError_t launch_reset_state(const Dev& d, hipStream_t s) {
   if (e == hipSuccess && d.cnt) e = launch_fill_u32(reinterpret_cast<uint32_t*>(d.cnt), 0u, d.total_rows, s);
   if (e == hipSuccess && d.acc_slot) e = launch_fill_u32(reinterpret_cast<uint32_t*>(d.acc_slot), 0u, d.total_slots, s);
   if (e == hipSuccess && d.acc_rows) e = launch_fill_u32(reinterpret_cast<uint32_t*>(d.acc_rows), 0u, d.total_rows, s);
-  if (e == hipSuccess) e = launch_fill_u32(reinterpret_cast<uint32_t*>(d.stats), 0u, (int64_t)d.T * kNStat * 2, s);
+  if (e == hipSuccess) e = launch_fill_u32(reinterpret_cast<uint32_t*>(d.stats), 0u,
+                                           ((int64_t)d.T << d.stat_shift) * kStatStride * 2, s);
   if (e == hipSuccess) e = launch_fill_u32(reinterpret_cast<uint32_t*>(d.err), 0u, 1, s);
   return e;
 }
@@ -116,6 +117,7 @@ constexpr int kFwdUnroll = 2;
 // lane, 2 waves per SIMD) is faster than 4 at 4 waves (355 -> 332 us on the industrial
 // workload; 8: 334 us, 12: 531 us); a step of few lookups wants the waves instead.
 constexpr int kProbeUnroll = 6, kProbeUnrollSmall = 4;
+constexpr int kProbeSums = 64;  // segments of an XCD whose counts a workgroup gathers in LDS
 constexpr int64_t kProbeSmallBelow = 1 << 21;  // lookups per call
 
 // QL = assoc/W lanes share one lookup (W = assoc up to 8 ways, 8 at 16 ways, 16 beyond),
@@ -128,6 +130,9 @@ template <int W, int PU>
 __global__ __launch_bounds__(256) void k_fwd_probe(Dev dv, const int32_t* __restrict__ idx, int64_t L,
                                                    const int32_t* __restrict__ off, int32_t B,
                                                    int32_t* __restrict__ src) {
+  __shared__ uint32_t sums[kProbeSums][3];  // counts of the XCD's first segments
+  for (int i = threadIdx.x; i < 3 * kProbeSums; i += blockDim.x) sums[i / 3][i % 3] = 0;
+  __syncthreads();
   const XcdSplit xs(dv.T);
   const int64_t tid = xs.unit * blockDim.x + threadIdx.x, stride = xs.units * blockDim.x;
   if (blockIdx.x == 0) {
@@ -220,7 +225,7 @@ __global__ __launch_bounds__(256) void k_fwd_probe(Dev dv, const int32_t* __rest
         }
       }
     }
-    // statistics of the segment: one atomic per wave and counter
+    // statistics of the segment, gathered in LDS for the workgroup
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
       ok += __shfl_xor(ok, o);
@@ -228,14 +233,25 @@ __global__ __launch_bounds__(256) void k_fwd_probe(Dev dv, const int32_t* __rest
       bad += __shfl_xor(bad, o);
     }
     if ((threadIdx.x & 63) == 0) {
-      unsigned long long* st = dv.stats + (int64_t)t * kNStat;
-      if (ok) atomicAdd(st + kStLookups, (unsigned long long)ok);
-      if (hit) atomicAdd(st + kStHitLookups, (unsigned long long)hit);
-      if (bad) {
-        atomicAdd(st + kStInvalidFwd, (unsigned long long)bad);
-        atomicOr(dv.err, kErrIndex);
+      const int i = (seg - xs.xcd) / kXcds;
+      if (i < kProbeSums) {
+        if (ok) atomicAdd(&sums[i][0], ok);
+        if (hit) atomicAdd(&sums[i][1], hit);
+        if (bad) atomicAdd(&sums[i][2], bad);
+      } else {
+        unsigned long long* st = stat_of(dv, t);
+        if (ok) atomicAdd(st + kStLookups, (unsigned long long)ok);
+        if (hit) atomicAdd(st + kStHitLookups, (unsigned long long)hit);
+        if (bad) atomicAdd(st + kStInvalidFwd, (unsigned long long)bad);
       }
+      if (bad) atomicOr(dv.err, kErrIndex);
     }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 3 * kProbeSums; i += blockDim.x) {
+    const uint32_t v = sums[i / 3][i % 3];
+    const int f = i % 3 == 0 ? kStLookups : i % 3 == 1 ? kStHitLookups : kStInvalidFwd;
+    if (v) atomicAdd(stat_of(dv, (xs.xcd + kXcds * (i / 3)) / xs.parts) + f, (unsigned long long)v);
   }
 }
 
@@ -329,17 +345,14 @@ __global__ __launch_bounds__(256) void k_fwd_gather(Dev dv, const int32_t* __res
   }
 }
 
-__global__ void k_zero_fwd_stats(Dev dv) {
-  for (int i = threadIdx.x; i < dv.T; i += blockDim.x) {
-    dv.stats[(int64_t)i * kNStat + kStLookups] = 0;
-    dv.stats[(int64_t)i * kNStat + kStHitLookups] = 0;
-    dv.stats[(int64_t)i * kNStat + kStInvalidFwd] = 0;
-  }
+__global__ __launch_bounds__(256) void k_zero_fwd_stats(Dev dv) {
+  zero_stats(dv, kStLookups, kStHitLookups);
+  zero_stats(dv, kStInvalidFwd, kStInvalidFwd);
 }
 
 hipError_t launch_forward(const Dev& d, const Work& w, const int32_t* idx, int64_t L, const int32_t* off, int32_t B,
                           float* out, hipStream_t s) {
-  k_zero_fwd_stats<<<1, 256, 0, s>>>(d);
+  k_zero_fwd_stats<<<grid_for((int64_t)d.T << d.stat_shift), 256, 0, s>>>(d);
   const int64_t nbags = (int64_t)d.T * B;
   if (nbags == 0) return hipGetLastError();
   k_check_offsets<<<grid_for(nbags, 2048), 256, 0, s>>>(d, off, nbags, L, w.ctr);

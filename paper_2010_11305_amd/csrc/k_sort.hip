@@ -777,9 +777,9 @@ __global__ __launch_bounds__(256) void k_expand(Dev dv, const int32_t* __restric
         } else {
           key = (uint32_t)(td.key_base + r);
         }
-        if (t == t_run) ++n_ok; else atomicAdd(&dv.stats[(int64_t)t * kNStat + kStBwdLookups], 1ull);
+        if (t == t_run) ++n_ok; else atomicAdd(stat_of(dv, t) + kStBwdLookups, 1ull);
       } else {
-        if (t == t_run) ++n_bad; else atomicAdd(&dv.stats[(int64_t)t * kNStat + kStInvalidBwd], 1ull);
+        if (t == t_run) ++n_bad; else atomicAdd(stat_of(dv, t) + kStInvalidBwd, 1ull);
         atomicOr(dv.err, kErrIndex);
       }
       keys[p] = key;
@@ -818,8 +818,8 @@ __global__ __launch_bounds__(256) void k_expand(Dev dv, const int32_t* __restric
       n_ok += __shfl_xor(n_ok, o);
       n_bad += __shfl_xor(n_bad, o);
     }
-    if (lane == 0 && n_ok) atomicAdd(&dv.stats[(int64_t)t_run * kNStat + kStBwdLookups], (unsigned long long)n_ok);
-    if (lane == 0 && n_bad) atomicAdd(&dv.stats[(int64_t)t_run * kNStat + kStInvalidBwd], (unsigned long long)n_bad);
+    if (lane == 0 && n_ok) atomicAdd(stat_of(dv, t_run) + kStBwdLookups, (unsigned long long)n_ok);
+    if (lane == 0 && n_bad) atomicAdd(stat_of(dv, t_run) + kStInvalidBwd, (unsigned long long)n_bad);
   }
   if constexpr (SEG) {
 #pragma unroll

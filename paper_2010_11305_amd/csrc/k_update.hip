@@ -26,12 +26,10 @@ constexpr int32_t kActDone = 4;  // row fully handled by k_policy
 constexpr int kUnroll = 2;  // independent row loads in flight per row group
 constexpr int64_t kSpreadBelow = 1 << 21;  // lookups per step below which SPREAD kernels run
 
-__global__ void k_bwd_begin(Dev dv, unsigned long long* ctr, int64_t L) {
-  for (int i = threadIdx.x; i < dv.T; i += blockDim.x) {
-    for (int f = kStBwdLookups; f <= kStHitEvictions; ++f) dv.stats[(int64_t)i * kNStat + f] = 0;
-    dv.stats[(int64_t)i * kNStat + kStInvalidBwd] = 0;
-  }
-  if (threadIdx.x == 0) {
+__global__ __launch_bounds__(256) void k_bwd_begin(Dev dv, unsigned long long* ctr, int64_t L) {
+  zero_stats(dv, kStBwdLookups, kStHitEvictions);
+  zero_stats(dv, kStInvalidBwd, kStInvalidBwd);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
     for (int c = 0; c < kNCounters; ++c) ctr[c] = 0;
     ctr[kCValid] = (unsigned long long)L;
   }
@@ -587,7 +585,7 @@ __global__ __launch_bounds__(256) void k_tab_first(Dev dv, Work w, int T) {
   w.tab_first[t] = (int32_t)lo;
   if (t < T) {
     const int64_t n = hi - lo;
-    unsigned long long* st = dv.stats + (int64_t)t * kNStat;
+    unsigned long long* st = stat_of(dv, t);
     st[kStUnique] = (unsigned long long)n;
     if (dv.desc[t].n_sets == 0) st[kStBypasses] = (unsigned long long)n;
   }
@@ -717,19 +715,25 @@ struct PolicyLds {
   long long vic_pv[64];
 };
 
-// Statistics of the sets a wave handles, accumulated while the table does not change.
+// Statistics of the sets a row group handles, accumulated while the table does not change.
 struct PolicyStats {
+  static constexpr int kN = 6;
   int t = -1;
   uint32_t ins = 0, byp = 0, ev = 0, em = 0, he = 0, hits = 0;
-  __device__ void flush(unsigned long long* stats) {
+  __device__ static int field(int i) {
+    constexpr int f[kN] = {kStUniqueHits, kStInserts, kStBypasses, kStEvictions, kStEmptyFills, kStHitEvictions};
+    return f[i];
+  }
+  __device__ void get(uint32_t (&v)[kN]) const {
+    v[0] = hits; v[1] = ins; v[2] = byp; v[3] = ev; v[4] = em; v[5] = he;
+  }
+  __device__ void flush(const Dev& dv) {
     if (t < 0) return;
-    unsigned long long* s = stats + (int64_t)t * kNStat;
-    if (hits) atomicAdd(s + kStUniqueHits, (unsigned long long)hits);
-    if (ins) atomicAdd(s + kStInserts, (unsigned long long)ins);
-    if (byp) atomicAdd(s + kStBypasses, (unsigned long long)byp);
-    if (ev) atomicAdd(s + kStEvictions, (unsigned long long)ev);
-    if (em) atomicAdd(s + kStEmptyFills, (unsigned long long)em);
-    if (he) atomicAdd(s + kStHitEvictions, (unsigned long long)he);
+    unsigned long long* s = stat_of(dv, t);
+    uint32_t v[kN];
+    get(v);
+    for (int i = 0; i < kN; ++i)
+      if (v[i]) atomicAdd(s + field(i), (unsigned long long)v[i]);
     ins = byp = ev = em = he = hits = 0;
   }
 };
@@ -765,7 +769,7 @@ __global__ __launch_bounds__(256) void k_policy(Dev dv, Work w, uint32_t step) {
     const int64_t sbase = td.slot_base + (r0 % td.n_sets) * A;
 
     if (t != ps.t) {
-      if (l == 0) ps.flush(dv.stats);
+      if (l == 0) ps.flush(dv);
       ps.t = t;
     }
     // residents that hit this step, and the number of missed rows
@@ -900,7 +904,7 @@ __global__ __launch_bounds__(256) void k_policy(Dev dv, Work w, uint32_t step) {
     }
     const uint32_t n_valid = (uint32_t)__popcll(__ballot(l < n_ins && my_old >= 0) & gmask);
     const uint32_t n_hitev = (uint32_t)__popcll(__ballot(l < n_ins && my_hu >= 0) & gmask);
-    if (l == 0 && n_hitev) atomicAdd(&w.ctr[kCHitEv], (unsigned long long)n_hitev);
+    if (l == 0 && n_hitev) w.ctr[kCHitEv] = 1;
     if (l == 0) {
       ps.ins += (uint32_t)n_ins;
       ps.byp += (uint32_t)(M - n_ins);
@@ -909,7 +913,26 @@ __global__ __launch_bounds__(256) void k_policy(Dev dv, Work w, uint32_t step) {
       ps.he += n_hitev;
     }
   }
-  if (l == 0) ps.flush(dv.stats);
+  // the last tables: the groups of one table as the workgroup's first group are summed in
+  // LDS and added once; the others add their own
+  __shared__ int32_t tab_s;
+  __shared__ uint32_t sums_s[PolicyStats::kN];
+  if (threadIdx.x == 0) tab_s = ps.t;
+  if (threadIdx.x < PolicyStats::kN) sums_s[threadIdx.x] = 0;
+  __syncthreads();
+  if (l == 0 && ps.t >= 0) {
+    if (ps.t == tab_s) {
+      uint32_t v[PolicyStats::kN];
+      ps.get(v);
+      for (int i = 0; i < PolicyStats::kN; ++i)
+        if (v[i]) atomicAdd(&sums_s[i], v[i]);
+    } else {
+      ps.flush(dv);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < PolicyStats::kN && sums_s[threadIdx.x])
+    atomicAdd(stat_of(dv, tab_s) + PolicyStats::field(threadIdx.x), (unsigned long long)sums_s[threadIdx.x]);
 }
 
 // ---- displaced residents -> T -----------------------------------------------------------------
@@ -1102,7 +1125,7 @@ hipError_t launch_backward(const Dev& d, const Work& w, const int32_t* idx, int6
                            const float* grad, uint64_t step64, int key_bits, int seg_passes, bool decay,
                            const hipEvent_t* update_events, const SideStream& side, hipStream_t s) {
   const uint32_t step = (uint32_t)step64;
-  k_bwd_begin<<<1, 256, 0, s>>>(d, w.ctr, L);
+  k_bwd_begin<<<grid_for((int64_t)d.T << d.stat_shift), 256, 0, s>>>(d, w.ctr, L);
   // offsets first: a rejected call must not reach the decay either
   const int64_t nbags = (int64_t)d.T * B;
   k_check_offsets<<<grid_for(nbags, 2048), 256, 0, s>>>(d, off, nbags, L, w.ctr);
@@ -1153,16 +1176,21 @@ hipError_t launch_backward(const Dev& d, const Work& w, const int32_t* idx, int6
     // packing of the row update's inputs on the side stream, after the decisions: the
     // block sums beside the eviction 1111 -> 1434 us)
     const bool cached = d.total_slots > 0;
+    const hipStream_t s2 = side.s;
     if (cached) {
-      hipError_t e2 = hipEventRecord(side.fork, s);
-      if (e2 == hipSuccess) e2 = hipStreamWaitEvent(side.s, side.fork, 0);
-      if (e2 != hipSuccess) return e2;
-      if (d.assoc <= 16) k_policy<16><<<grid(k_policy<16>), 256, 0, side.s>>>(d, w, step);
-      else if (d.assoc <= 32) k_policy<32><<<grid(k_policy<32>), 256, 0, side.s>>>(d, w, step);
-      else k_policy<64><<<grid(k_policy<64>), 256, 0, side.s>>>(d, w, step);
-      k_evict<D, BITS, SB16, false><<<grid(k_evict<D, BITS, SB16, false>), 256, 0, side.s>>>(d, w, sv, grad, step);
-      e2 = hipEventRecord(side.join, side.s);
-      if (e2 != hipSuccess) return e2;
+      if (s2 != s) {
+        hipError_t e2 = hipEventRecord(side.fork, s);
+        if (e2 == hipSuccess) e2 = hipStreamWaitEvent(s2, side.fork, 0);
+        if (e2 != hipSuccess) return e2;
+      }
+      if (d.assoc <= 16) k_policy<16><<<grid(k_policy<16>), 256, 0, s2>>>(d, w, step);
+      else if (d.assoc <= 32) k_policy<32><<<grid(k_policy<32>), 256, 0, s2>>>(d, w, step);
+      else k_policy<64><<<grid(k_policy<64>), 256, 0, s2>>>(d, w, step);
+      k_evict<D, BITS, SB16, false><<<grid(k_evict<D, BITS, SB16, false>), 256, 0, s2>>>(d, w, sv, grad, step);
+      if (s2 != s) {
+        const hipError_t e2 = hipEventRecord(side.join, s2);
+        if (e2 != hipSuccess) return e2;
+      }
     }
     if (spread) k_partials<D, true><<<grid(k_partials<D, true>), 256, 0, s>>>(d, w, sv, grad);
     else k_partials<D, false><<<grid(k_partials<D, false>), 256, 0, s>>>(d, w, sv, grad);
@@ -1172,8 +1200,10 @@ hipError_t launch_backward(const Dev& d, const Work& w, const int32_t* idx, int6
       k_block_fold<D><<<grid(k_block_fold<D>), 256, 0, s>>>(w, nblk);
     }
     if (cached) {
-      const hipError_t e2 = hipStreamWaitEvent(s, side.join, 0);
-      if (e2 != hipSuccess) return e2;
+      if (s2 != s) {
+        const hipError_t e2 = hipStreamWaitEvent(s, side.join, 0);
+        if (e2 != hipSuccess) return e2;
+      }
       // a resident hit this step is displaced only under LFU or in a direct-mapped LRU
       // cache (under LRU a hit takes the step's stamp, which no candidate exceeds)
       if (d.policy != 0 || d.assoc == 1)

@@ -175,7 +175,7 @@ int plan_config(const emb_cache_config* c, Plan* p) {
   p->o_accr = take(c->optimizer == EMB_OPT_ROWWISE_ADAGRAD && !p->acc_in_rec ? (size_t)rows * 4 : 0);
   p->o_desc = take(sizeof(TableDesc) * T);
   p->o_keyb = take(sizeof(int64_t) * (T + 1));
-  p->o_stats = take(sizeof(unsigned long long) * T * embc::kNStat);
+  p->o_stats = take(sizeof(unsigned long long) * embc::kStatStride * ((size_t)T << embc::stat_shift_for(T)));
   p->o_err = take(kAlign);
   // the low-precision table comes last: a caller may place it in a buffer of its own
   p->o_rec = take((size_t)rows * p->rec_bytes);
@@ -410,6 +410,7 @@ int create_impl(const emb_cache_config* cfg, void* state, size_t state_bytes, vo
   d.policy = cfg->policy;
   d.rounding = cfg->rounding;
   d.optimizer = cfg->optimizer;
+  d.stat_shift = embc::stat_shift_for(cfg->num_tables);
   d.lr = cfg->lr;
   d.eps = cfg->eps;
   d.seed = cfg->seed;
@@ -529,11 +530,16 @@ int emb_cache_backward_update(emb_cache_t h, const int32_t* indices, int64_t num
 int emb_cache_get_stats(emb_cache_t h, int32_t table, int64_t* out, void* stream) {
   if (!h || !out || table < 0 || table >= h->cfg.num_tables) return EMB_EINVAL;
   hipStream_t s = S(stream);
-  unsigned long long tmp[embc::kNStat];
-  hipError_t e = hipMemcpyAsync(tmp, h->dev.stats + (int64_t)table * embc::kNStat, sizeof(tmp), hipMemcpyDeviceToHost, s);
+  unsigned long long tmp[embc::kStatStride << embc::kMaxStatShift];
+  const int copies = 1 << h->dev.stat_shift;
+  const size_t words = (size_t)copies * embc::kStatStride;
+  hipError_t e = hipMemcpyAsync(tmp, h->dev.stats + table * words, sizeof(*tmp) * words, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return EMB_EHIP;
-  for (int i = 0; i < embc::kNStat; ++i) out[i] = (int64_t)tmp[i];
+  for (int i = 0; i < embc::kNStat; ++i) {
+    out[i] = 0;
+    for (int c = 0; c < copies; ++c) out[i] += (int64_t)tmp[c * embc::kStatStride + i];
+  }
   return EMB_OK;
 }
 
