@@ -1,5 +1,6 @@
 // State reset, uniform initialisation, and the forward pass:
 // pooled[b][t] = sum over the bag of fetch(T_t, C_t, i) (Sec. 3 fetch operator).
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <type_traits>
@@ -104,20 +105,25 @@ hipError_t launch_init_uniform(const Dev& d, float lo, float hi, uint64_t init_s
 }
 
 // ---- forward --------------------------------------------------------------------------
-// Two passes.  k_fwd_probe: one lane per lookup up to 8 ways, 2 lanes for 16 or 32, 4 for 64
-// (tables split over the XCDs), checks the row, probes its set, and write a code: the cache slot (hit), -2-row (miss) or
+// Two passes.  k_fwd_probe: one lane per lookup up to 8 ways, 2 lanes for 16 or 32, 4 for 64,
+// checks the row, probes its set, and write a code: the cache slot (hit), -2-row (miss) or
 // -1 (skipped).  k_fwd_gather: one group of LPR
 // lanes per bag (64/LPR bags per wave), tables split over the XCDs; lane j reads the
 // code of position j of each chunk of LPR positions, the rows are fetched FU at a time
 // (all FU loads issued before any is used) and summed left to right.  A bag with no
 // valid lookup gives +0.
+// Both take their work flat: the positions (probe) and tiles of 256/LPR bags (gather) of all
+// tables, one contiguous run per XCD, so that a call of few bags per table, or of a number of
+// tables that is no multiple of 8, still fills every XCD.  With one table at a time per XCD,
+// 100 tables of 512 bags (1.5M lookups) took 275 us and take 79; 10 tables of 16384 bags
+// 307 and 205; full tables are as before (100 tables of 16384 bags: 1.78 ms).
 constexpr int kFwdUnroll = 2;
 
 // Lookups in flight per lane group of the probe (PU).  On a large step 6 (96 tags per
 // lane, 2 waves per SIMD) is faster than 4 at 4 waves (355 -> 332 us on the industrial
 // workload; 8: 334 us, 12: 531 us); a step of few lookups wants the waves instead.
 constexpr int kProbeUnroll = 6, kProbeUnrollSmall = 4;
-constexpr int kProbeSums = 64;  // segments of an XCD whose counts a workgroup gathers in LDS
+constexpr int kProbeSums = 64;  // tables of a range whose counts a workgroup gathers in LDS
 constexpr int64_t kProbeSmallBelow = 1 << 21;  // lookups per call
 
 // QL = assoc/W lanes share one lookup (W = assoc up to 8 ways, 8 at 16 ways, 16 beyond),
@@ -130,29 +136,39 @@ template <int W, int PU>
 __global__ __launch_bounds__(256) void k_fwd_probe(Dev dv, const int32_t* __restrict__ idx, int64_t L,
                                                    const int32_t* __restrict__ off, int32_t B,
                                                    int32_t* __restrict__ src) {
-  __shared__ uint32_t sums[kProbeSums][3];  // counts of the XCD's first segments
+  __shared__ uint32_t sums[kProbeSums][3];  // counts of the range's first tables
   for (int i = threadIdx.x; i < 3 * kProbeSums; i += blockDim.x) sums[i / 3][i % 3] = 0;
   __syncthreads();
-  const XcdSplit xs(dv.T);
-  const int64_t tid = xs.unit * blockDim.x + threadIdx.x, stride = xs.units * blockDim.x;
+  const int64_t pfirst = min<int64_t>(max<int64_t>(off[0], 0), L);
+  const int64_t plast = min<int64_t>(max<int64_t>(off[(int64_t)dv.T * B], pfirst), L);
   if (blockIdx.x == 0) {
     // positions outside every bag are skipped
-    const int64_t first = min<int64_t>(max<int64_t>(off[0], 0), L);
-    const int64_t last = min<int64_t>(max<int64_t>(off[(int64_t)dv.T * B], first), L);
-    for (int64_t p = threadIdx.x; p < first; p += blockDim.x) src[p] = -1;
-    for (int64_t p = last + threadIdx.x; p < L; p += blockDim.x) src[p] = -1;
+    for (int64_t p = threadIdx.x; p < pfirst; p += blockDim.x) src[p] = -1;
+    for (int64_t p = plast + threadIdx.x; p < L; p += blockDim.x) src[p] = -1;
   }
+  // workgroup -> contiguous range of positions, XCD-major
+  const int64_t place = (int64_t)(blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds;
+  int64_t pa, pb;
+  part_range(pfirst, plast, (int)place, (int)gridDim.x, pa, pb);
   const int A = dv.assoc;
   const int QL = A / W;  // 1 up to 16 ways, 2 or 4 for 32 or 64
   const int sub = threadIdx.x % QL;
-  const int64_t ptid = tid / QL, pstride = stride / QL;
-  for (int seg = xs.xcd; seg < xs.segments(dv.T); seg += kXcds) {
-    const int t = seg / xs.parts;
+  const int64_t ptid = threadIdx.x / QL, pstride = blockDim.x / QL;
+  // the range's first table: the last one that starts at or before it, searched by the
+  // whole wave (64 tables per round; with malformed offsets some table, or none, is found)
+  int t0 = 0;
+  for (int hi = dv.T; hi - t0 > 1;) {
+    const int step = (hi - t0 + 63) / 64, c = t0 + (int)(threadIdx.x & 63) * step;
+    const uint64_t le = __ballot(c == t0 || (c < hi && off[(int64_t)c * B] <= pa));
+    t0 += (63 - (int)__clzll((unsigned long long)le)) * step;
+    hi = min(hi, t0 + step);
+  }
+  for (int t = t0; t < dv.T; ++t) {
     const TableDesc td = dv.desc[t];
     const int64_t a = min<int64_t>(max<int64_t>(off[(int64_t)t * B], 0), L);
     const int64_t b = min<int64_t>(max<int64_t>(off[(int64_t)(t + 1) * B], a), L);
-    int64_t lo, hi;
-    part_range(a, b, seg % xs.parts, xs.parts, lo, hi);
+    if (a >= pb) break;
+    const int64_t lo = max<int64_t>(a, pa), hi = min<int64_t>(b, pb);
     const int32_t* tags = dv.tag + td.slot_base + sub * W;
     uint32_t ok = 0, hit = 0, bad = 0;
     // the index loads run one iteration ahead of the tag loads, and every load is
@@ -225,7 +241,7 @@ __global__ __launch_bounds__(256) void k_fwd_probe(Dev dv, const int32_t* __rest
         }
       }
     }
-    // statistics of the segment, gathered in LDS for the workgroup
+    // statistics of the table, gathered in LDS for the workgroup
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
       ok += __shfl_xor(ok, o);
@@ -233,7 +249,7 @@ __global__ __launch_bounds__(256) void k_fwd_probe(Dev dv, const int32_t* __rest
       bad += __shfl_xor(bad, o);
     }
     if ((threadIdx.x & 63) == 0) {
-      const int i = (seg - xs.xcd) / kXcds;
+      const int i = t - t0;
       if (i < kProbeSums) {
         if (ok) atomicAdd(&sums[i][0], ok);
         if (hit) atomicAdd(&sums[i][1], hit);
@@ -251,42 +267,60 @@ __global__ __launch_bounds__(256) void k_fwd_probe(Dev dv, const int32_t* __rest
   for (int i = threadIdx.x; i < 3 * kProbeSums; i += blockDim.x) {
     const uint32_t v = sums[i / 3][i % 3];
     const int f = i % 3 == 0 ? kStLookups : i % 3 == 1 ? kStHitLookups : kStInvalidFwd;
-    if (v) atomicAdd(stat_of(dv, (xs.xcd + kXcds * (i / 3)) / xs.parts) + f, (unsigned long long)v);
+    if (v) atomicAdd(stat_of(dv, t0 + i / 3) + f, (unsigned long long)v);
   }
 }
 
 template <int D, int BITS, bool SB16>
 __global__ __launch_bounds__(256) void k_fwd_gather(Dev dv, const int32_t* __restrict__ src, int64_t L,
-                                                    const int32_t* __restrict__ off, int32_t B,
+                                                    const int32_t* __restrict__ off, int32_t B, DivConst per_table,
                                                     float* __restrict__ out) {
   constexpr int LPR = Geo<D>::LPR, FU = kFwdUnroll;
   constexpr int GPB = 256 / LPR;
   const int64_t RB = dv.rec_bytes;
   const int g = threadIdx.x & (LPR - 1);
-  const XcdSplit xs(dv.T);
-  const int64_t gx = xs.unit * GPB + threadIdx.x / LPR, gstride = xs.units * GPB;
-  for (int seg = xs.xcd; seg < xs.segments(dv.T); seg += kXcds) {
-    const int t = seg / xs.parts;
-    int64_t blo, bhi;
-    part_range(0, B, seg % xs.parts, xs.parts, blo, bhi);
-    const TableDesc td = dv.desc[t];
-    const uint8_t* rec0 = dv.rec + td.row_base * RB;
-    // codes outside this table's slots and rows are skipped (only malformed offsets
-    // produce them); slots, rows and positions are below 2^31 (32-bit arithmetic)
-    const int32_t slot_lo = (int32_t)td.slot_base, slot_hi = (int32_t)(td.slot_base + td.n_sets * dv.assoc);
-    const int32_t nrows = (int32_t)td.N;
-    if (blo + gx >= bhi) continue;
-    // the offsets of the group's next bag are loaded one bag ahead, the codes of the
-    // next LPR positions one chunk ahead (indices clamped so that the loads are
-    // unconditional; a clamped load is not used)
-    const int32_t* offt = off + (int64_t)t * B;
-    int64_t o0 = offt[blo + gx], o1 = offt[blo + gx + 1];
-    for (int64_t b = blo + gx; b < bhi; b += gstride) {
+  // tiles of GPB bags of one table, table-major: a contiguous run of tiles per XCD, which
+  // its workgroups walk side by side
+  const int xcd = blockIdx.x % kXcds, unit = blockIdx.x / kXcds, units = gridDim.x / kXcds;
+  const int64_t ntiles = (int64_t)per_table.d * dv.T;
+  int64_t clo, chi;
+  part_range(0, ntiles, xcd, kXcds, clo, chi);
+  if (clo + unit >= chi) return;
+  const auto tile_bag = [&](int64_t c, int& t) -> uint32_t {
+    t = (int)div_by((uint32_t)c, per_table);
+    return ((uint32_t)c - (uint32_t)t * per_table.d) * GPB + threadIdx.x / LPR;
+  };
+  const uint32_t last = (uint32_t)B - 1u;
+  // the offsets of the group's next bag are loaded one tile ahead, the codes of the next
+  // LPR positions one chunk ahead (indices clamped so that the loads are unconditional; a
+  // clamped load is not used)
+  int tn;
+  uint32_t bn = tile_bag(clo + unit, tn);
+  int64_t o0 = off[(int64_t)tn * B + min(bn, last)], o1 = off[(int64_t)tn * B + min(bn, last) + 1];
+  int t = -1;
+  const uint8_t* rec0 = nullptr;
+  int32_t slot_lo = 0, slot_hi = 0, nrows = 0;
+  for (int64_t c = clo + unit; c < chi; c += units) {
+    {
+      if (tn != t) {  // whole workgroup
+        t = tn;
+        // codes outside this table's slots and rows are skipped (only malformed offsets
+        // produce them); slots, rows and positions are below 2^31 (32-bit arithmetic)
+        const TableDesc& td = dv.desc[t];
+        rec0 = dv.rec + td.row_base * RB;
+        slot_lo = (int32_t)td.slot_base, slot_hi = (int32_t)(td.slot_base + td.n_sets * dv.assoc);
+        nrows = (int32_t)td.N;
+      }
+      const uint32_t b = bn;
       const int64_t p0 = o0 < 0 ? 0 : o0;
       const int64_t p1 = o1 > L ? L : o1;
-      const int64_t nb = min<int64_t>(b + gstride, bhi - 1);
-      o0 = offt[nb];
-      o1 = offt[nb + 1];
+      bn = tile_bag(min<int64_t>(c + units, chi - 1), tn);
+      {
+        const int64_t nb = (int64_t)tn * B + min(bn, last);
+        o0 = off[nb];
+        o1 = off[nb + 1];
+      }
+      if (b > last) continue;  // past the table's last bag
       // the sum starts from -0, the identity of IEEE addition (adding the first term
       // gives exactly that term, as in the seeded left-to-right sum); a bag without a
       // valid lookup gives +0
@@ -345,30 +379,195 @@ __global__ __launch_bounds__(256) void k_fwd_gather(Dev dv, const int32_t* __res
   }
 }
 
-__global__ __launch_bounds__(256) void k_zero_fwd_stats(Dev dv) {
+// Zeroes the forward statistics and checks the offsets: one launch before the kernels that
+// count.
+__global__ __launch_bounds__(256) void k_fwd_begin(Dev dv, const int32_t* __restrict__ off, int64_t nbags, int64_t L) {
   zero_stats(dv, kStLookups, kStHitLookups);
   zero_stats(dv, kStInvalidFwd, kStInvalidFwd);
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nbags; i += stride) {
+    const int64_t a = off[i], b = off[i + 1];
+    if (a < 0 || b < a || b > L) atomicOr(dv.err, kErrOffsets);
+  }
+}
+
+// ---- forward of small calls ------------------------------------------------------------------
+// One kernel probes and gathers: a row group per bag; lane j of the group probes position j
+// of each run of LPR positions (all the set's tags in flight), then the rows are fetched
+// FU at a time and summed left to right, as in k_fwd_gather.  Such a call waits on its
+// chain of dependent loads and on launches (about 5 us each): 26 tables of 256 one-lookup
+// bags take 12 us in two launches against 18 in three, 12 tables of 1000 20-lookup bags
+// (0.24M lookups) 19 against 25.  From about 0.3M lookups on the chip is full and two
+// passes are faster, each with more waves in flight than this kernel's registers allow
+// (0.49M lookups: 33 us against 27, 1.5M: 114 against 79).
+// Bags are taken flat, table-major, in one contiguous range per XCD and per workgroup, so
+// that a workgroup meets few tables and every XCD has the same number of bags.
+constexpr int kFusedUnroll = 4;  // rows in flight per row group
+constexpr int64_t kFusedBelow = 1 << 18;  // lookups per call
+
+template <int D, int BITS, bool SB16, int MAXA>
+__global__ __launch_bounds__(256) void k_fwd_fused(Dev dv, const int32_t* __restrict__ idx, int64_t L,
+                                                   const int32_t* __restrict__ off, int32_t B, DivConst byB,
+                                                   float* __restrict__ out) {
+  constexpr int LPR = Geo<D>::LPR, FU = kFusedUnroll, GPB = 256 / LPR;
+  __shared__ uint32_t sum_s[4][3];
+  __shared__ int tab_s[4];
+  const int64_t RB = dv.rec_bytes;
+  const int g = threadIdx.x & (LPR - 1);
+  const int64_t nbags = (int64_t)dv.T * B;
+  // workgroup -> contiguous range of bags, XCD-major
+  const int64_t place = (int64_t)(blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds;
+  int64_t blo, bhi;
+  part_range(0, nbags, (int)place, (int)gridDim.x, blo, bhi);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  int t = -1;
+  TableDesc td{};
+  uint32_t n_ok = 0, n_hit = 0, n_bad = 0;
+  const auto flush_lane = [&]() {  // a group that goes on to another table
+    unsigned long long* st = stat_of(dv, t);
+    if (n_ok) atomicAdd(st + kStLookups, (unsigned long long)n_ok);
+    if (n_hit) atomicAdd(st + kStHitLookups, (unsigned long long)n_hit);
+    if (n_bad) {
+      atomicAdd(st + kStInvalidFwd, (unsigned long long)n_bad);
+      atomicOr(dv.err, kErrIndex);
+    }
+    n_ok = n_hit = n_bad = 0;
+  };
+  for (int64_t gbag = blo + threadIdx.x / LPR; gbag < bhi; gbag += GPB) {
+    const int tb = (int)div_by((uint32_t)gbag, byB);
+    if (tb != t) {
+      if (t >= 0) flush_lane();
+      t = tb;
+      td = dv.desc[t];
+    }
+    const int64_t o0 = off[gbag], o1 = off[gbag + 1];
+    const int64_t p0 = o0 < 0 ? 0 : o0;
+    const int64_t p1 = o1 > L ? L : o1;
+    const uint8_t* rec0 = dv.rec + td.row_base * RB;
+    float acc[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = -0.0f;
+    bool any = false;
+    for (int64_t pc = p0; pc < p1; pc += LPR) {
+      const int n = (int)min<int64_t>(LPR, p1 - pc);
+      int32_t code = -1;
+      if (g < n) {
+        const int32_t r = idx[pc + g];
+        if (r >= 0 && (int64_t)r < td.N) {
+          const int32_t sl = probe_slot<MAXA>(dv, td, r);
+          code = sl >= 0 ? sl : -2 - r;
+          ++n_ok;
+          n_hit += sl >= 0;
+        } else {
+          ++n_bad;
+        }
+      }
+      for (int j = 0; j < n; j += FU) {
+        float raw[FU][8];
+        RecRaw<D, BITS, SB16> rr[FU];
+        int kind[FU];  // 0 skip, 1 cache row, 2 low-precision row
+#pragma unroll
+        for (int q = 0; q < FU; ++q) {
+          const int32_t cq = __shfl(code, j + q, LPR);
+          kind[q] = j + q < n ? (cq >= 0 ? 1 : cq <= -2 ? 2 : 0) : 0;
+          if (kind[q] == 1) {
+            load_row<D>(dv.crow + (int64_t)cq * D, g, raw[q]);
+          } else if (kind[q] == 2) {
+            const uint8_t* rec = static_cast<const uint8_t*>(
+                __builtin_assume_aligned(rec0 + (int64_t)(-2 - cq) * RB, Rec<D, BITS, SB16>::ALIGN));
+            rr[q] = load_rec_raw<D, BITS, SB16>(rec, g);
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < FU; ++q) {
+          if (kind[q] == 0) continue;
+          if (kind[q] == 2) {
+            CodeWords<BITS> cw;
+            SbWords<SB16> sbw;
+            rec_words_unpack<D, BITS, SB16>(rr[q], cw, sbw);
+            float sq, bq;
+            decode_sb<SB16>(sbw, sq, bq);
+            dequant8<BITS>(row_code_words<D, BITS>(cw, g), sq, bq, raw[q]);
+          }
+#pragma unroll
+          for (int i = 0; i < 8; ++i) acc[i] = acc[i] + raw[q][i];
+          any = true;
+        }
+      }
+    }
+    if (!any) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] = 0.0f;
+    }
+    const int64_t b = gbag - (int64_t)t * B;
+    store_row_nt<D>(out + (b * dv.T + t) * D, g, acc);
+  }
+  // the last table's counts: one atomic per workgroup and counter (waves of one table)
+  const uint64_t has = __ballot(t >= 0);
+  const int t0 = has ? __shfl(t, (int)__builtin_ctzll(has)) : -1;
+  if (t >= 0 && t != t0) flush_lane();
+  if (n_bad) atomicOr(dv.err, kErrIndex);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    n_ok += __shfl_xor(n_ok, o);
+    n_hit += __shfl_xor(n_hit, o);
+    n_bad += __shfl_xor(n_bad, o);
+  }
+  if (lane == 0) {
+    tab_s[wv] = t0;
+    sum_s[wv][0] = n_ok;
+    sum_s[wv][1] = n_hit;
+    sum_s[wv][2] = n_bad;
+  }
+  __syncthreads();
+  if (threadIdx.x < 3) {
+    const int f = threadIdx.x == 0 ? kStLookups : threadIdx.x == 1 ? kStHitLookups : kStInvalidFwd;
+    uint32_t run = 0;
+    for (int w = 0; w < 4; ++w) {
+      run += sum_s[w][threadIdx.x];
+      if (w == 3 || tab_s[w + 1] != tab_s[w]) {
+        if (run && tab_s[w] >= 0) atomicAdd(stat_of(dv, tab_s[w]) + f, (unsigned long long)run);
+        run = 0;
+      }
+    }
+  }
 }
 
 hipError_t launch_forward(const Dev& d, const Work& w, const int32_t* idx, int64_t L, const int32_t* off, int32_t B,
                           float* out, hipStream_t s) {
-  k_zero_fwd_stats<<<grid_for((int64_t)d.T << d.stat_shift), 256, 0, s>>>(d);
   const int64_t nbags = (int64_t)d.T * B;
+  k_fwd_begin<<<grid_for(nbags, 2048), 256, 0, s>>>(d, off, nbags, L);
   if (nbags == 0) return hipGetLastError();
-  k_check_offsets<<<grid_for(nbags, 2048), 256, 0, s>>>(d, off, nbags, L, w.ctr);
+  if (L < kFusedBelow) {
+    const DivConst byB = div_const((uint32_t)B);
+    return dispatch_row(d.dim, d.bits, d.sb16, [&]<int D, int BITS, bool SB16>() -> hipError_t {
+      const int64_t wgs = (nbags * Geo<D>::LPR + 255) / 256;
+      const auto run = [&](auto kernel) {
+        const int64_t cap = resident_grid(reinterpret_cast<const void*>(kernel));
+        const int64_t blocks = std::min<int64_t>((wgs + 7) / 8 * 8, cap);
+        kernel<<<(unsigned)blocks, 256, 0, s>>>(d, idx, L, off, B, byB, out);
+      };
+      if (d.assoc <= 16) run(k_fwd_fused<D, BITS, SB16, 16>);
+      else run(k_fwd_fused<D, BITS, SB16, 64>);
+      return hipGetLastError();
+    });
+  }
   if (L > 0) {
-    const auto probe = [&](auto kernel) {
-      kernel<<<resident_grid(reinterpret_cast<const void*>(kernel)), 256, 0, s>>>(d, idx, L, off, B, w.fwd_src);
+    const auto probe = [&](auto kernel, int lookups) {
+      // a workgroup's round of lookups each, at most the resident count
+      const int64_t cap = resident_grid(reinterpret_cast<const void*>(kernel));
+      const int64_t blocks = std::min<int64_t>((L + lookups - 1) / lookups / 8 * 8 + 8, cap);
+      kernel<<<(unsigned)blocks, 256, 0, s>>>(d, idx, L, off, B, w.fwd_src);
     };
     const auto probe_w = [&](auto pu) {
       constexpr int PU = decltype(pu)::value;
       // tags per lane: the whole set up to 8 ways, 8 of 16 (two lanes per lookup), 16 beyond
       switch (d.assoc <= 8 ? d.assoc : d.assoc == 16 ? 8 : 16) {
-        case 1: probe(k_fwd_probe<1, PU>); return hipSuccess;
-        case 2: probe(k_fwd_probe<2, PU>); return hipSuccess;
-        case 4: probe(k_fwd_probe<4, PU>); return hipSuccess;
-        case 8: probe(k_fwd_probe<8, PU>); return hipSuccess;
-        case 16: probe(k_fwd_probe<16, PU>); return hipSuccess;
+        case 1: probe(k_fwd_probe<1, PU>, 256 * 1 / d.assoc * PU); return hipSuccess;
+        case 2: probe(k_fwd_probe<2, PU>, 256 * 2 / d.assoc * PU); return hipSuccess;
+        case 4: probe(k_fwd_probe<4, PU>, 256 * 4 / d.assoc * PU); return hipSuccess;
+        case 8: probe(k_fwd_probe<8, PU>, 256 * 8 / d.assoc * PU); return hipSuccess;
+        case 16: probe(k_fwd_probe<16, PU>, 256 * 16 / d.assoc * PU); return hipSuccess;
         default: return hipErrorInvalidValue;
       }
     };
@@ -377,12 +576,13 @@ hipError_t launch_forward(const Dev& d, const Work& w, const int32_t* idx, int64
     if (e != hipSuccess) return e;
   }
   return dispatch_row(d.dim, d.bits, d.sb16, [&]<int D, int BITS, bool SB16>() -> hipError_t {
-    // whole multiples of 8 workgroups (one per XCD), at most the resident count
-    const int64_t wgs = (nbags * Geo<D>::LPR + 255) / 256;
+    // one tile per workgroup, in whole multiples of 8 workgroups, at most the resident count
+    constexpr int GPB = 256 / Geo<D>::LPR;
+    const DivConst per_table = div_const((uint32_t)((B + GPB - 1) / GPB));
+    const int64_t tiles = (int64_t)per_table.d * d.T;
     const int64_t cap = resident_grid(reinterpret_cast<const void*>(k_fwd_gather<D, BITS, SB16>));
-    int64_t blocks = (wgs + 7) / 8 * 8;
-    blocks = blocks < 8 ? 8 : (blocks > cap ? cap : blocks);
-    k_fwd_gather<D, BITS, SB16><<<(unsigned)blocks, 256, 0, s>>>(d, w.fwd_src, L, off, B, out);
+    const int64_t blocks = std::min<int64_t>((tiles + 7) / 8 * 8, cap);
+    k_fwd_gather<D, BITS, SB16><<<(unsigned)blocks, 256, 0, s>>>(d, w.fwd_src, L, off, B, per_table, out);
     return hipGetLastError();
   });
 }
