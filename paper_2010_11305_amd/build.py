@@ -20,7 +20,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libembcache.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
-SOURCES = ["k_forward.hip", "k_sort.hip", "k_update.hip", "runtime.cpp"]
+SOURCES = ["k_forward.hip", "k_sort.hip", "k_update.hip", "k_small.hip", "runtime.cpp"]
 ARCH = "gfx950"
 
 FLAGS = [

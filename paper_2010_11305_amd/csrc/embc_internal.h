@@ -121,6 +121,33 @@ struct Dev {
   int64_t total_slots;
 };
 
+// Small calls (k_small.hip): three launches, in which one workgroup per table sorts the table's
+// lookups.  Measured steps (us), small against general path: 26 tables of 2048 lookups 47
+// and 208, 400 of 160: 60 and 286, 16 of 3600: 79 and 230, 4 of 15000 (128 columns) 180 and
+// 266, one of 16384: 92 and 166, but one of 32768: 213 and 164 -- past 16384 lookups in a
+// table its workgroup sorts in memory.  The host knows the number of lookups of all tables
+// together, so the line is drawn at 16384 per table on average and 65536 in all; a call whose
+// lookups are nearly all in one table is then at most 0.1 ms slower than on the general path.
+constexpr int64_t kSmallLookups = 65536;
+constexpr int64_t kSmallPerTable = 16384;
+constexpr int kSmallTables = 512;
+constexpr int32_t kSmallBags = 65536;
+constexpr bool small_call(int64_t L, int32_t B, int T) {
+  return L <= kSmallLookups && L <= kSmallPerTable * T && B <= kSmallBags && T <= kSmallTables;
+}
+
+// The lists of one table in a small call, at offsets that follow from pos: unique rows and
+// sets from pos on, chunk sums from pos/8, big rows from pos/512.
+struct TabInfo {
+  uint32_t pos;     // its first lookup
+  uint32_t rows;    // unique rows
+  uint32_t sets;    // touched sets (without a cache: runs of rows)
+  uint32_t chunks;  // chunk sums
+  uint32_t big;     // rows with more than kBlockAbove lookups
+  uint32_t bad;     // its offsets were rejected
+  uint32_t pad[2];
+};
+
 // Per-call temporaries carved from the caller's workspace buffer.
 struct Work {
   uint32_t* keysA;
@@ -148,8 +175,8 @@ struct Work {
   int32_t* uvic_u;       // [L] insert: unique index of that row if it was updated this step, else -1
   uint4* umeta;          // [L] per unique row, the inputs of the row update in one word (k_pack_meta)
   unsigned long long* ukey;  // [L] LFU: a missed row's rank key (count << 32 | ~row), 0 for a hit
-  float* partial;        // [L/32 + 2][dim] chunk sums
-  uint2* chunk_span;     // [L/32 + 2] occurrences [x, y) of the sorted stream summed by each chunk
+  float* partial;        // [max_partials][dim] chunk sums
+  uint2* chunk_span;     // [max_partials] occurrences [x, y) of the sorted stream summed by each chunk
   uint32_t* ubig;        // [L] 1 for a row with more than kBlockAbove lookups, then its exclusive prefix
   int32_t* big_rows;     // [max_big] unique row of each such row ("big row"), in unique-row order
   uint32_t* bbound;      // [max_big][bound_stride(max_nblk)] first occurrence of each stage of a big row
@@ -159,6 +186,7 @@ struct Work {
   int32_t* tab_first;    // [T+1] first unique row of each table (tab_first[T] = number of unique rows)
   int32_t* fwd_src;      // [L] forward: cache slot of each lookup, -2-row for a miss, -1 if skipped
   unsigned long long* ctr;  // counters, see kC*
+  TabInfo* tab_info;     // [T] small calls
   int64_t max_indices;
   int64_t max_partials;
 };
@@ -204,6 +232,11 @@ struct SideStream {
 hipError_t launch_backward(const Dev& d, const Work& w, const int32_t* idx, int64_t L, const int32_t* off,
                            int32_t B, const float* grad, uint64_t step, int key_bits, int seg_passes, bool decay,
                            const hipEvent_t* update_events, const SideStream& side, hipStream_t s);
+
+// The same step for a small_call; passes: 8-bit digits of the largest table's local keys.
+hipError_t launch_backward_small(const Dev& d, const Work& w, const int32_t* idx, int64_t L, const int32_t* off,
+                                 int32_t B, const float* grad, uint64_t step, int passes, bool decay,
+                                 const hipEvent_t* update_events, hipStream_t s);
 
 size_t sort_status_words(int64_t n, int T);
 size_t sort_seg_words(int T);

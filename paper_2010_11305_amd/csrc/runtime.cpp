@@ -86,7 +86,7 @@ struct Plan {
   size_t o_rec, o_crow, o_tag, o_ts, o_cnt, o_accs, o_accr, o_desc, o_keyb, o_stats, o_err, state_bytes, table_bytes;
   // workspace offsets
   size_t o_kA, o_vA, o_kB, o_vB, o_ssmall, o_sst0, o_sst1, o_sseg, o_part, o_tcnt, o_tpre, o_tthr, o_uk, o_seg, o_setf, o_urow, o_utab, o_uslot,
-      o_uact, o_udest, o_umeta, o_ukey, o_nch, o_cbase, o_uvrow, o_uvu, o_partial, o_span, o_ubig, o_brows, o_bbound, o_bpart, o_tabf, o_src, o_ctr, ws_bytes;
+      o_uact, o_udest, o_umeta, o_ukey, o_nch, o_cbase, o_uvrow, o_uvu, o_partial, o_span, o_ubig, o_brows, o_bbound, o_bpart, o_tabf, o_src, o_ctr, o_tabi, ws_bytes;
   int64_t max_partials = 0;
   int64_t max_big = 0;
   int32_t max_nblk = 0;
@@ -210,11 +210,12 @@ int plan_config(const emb_cache_config* c, Plan* p) {
   p->o_cbase = take(4 * (L + 1));
   p->o_uvrow = take(4 * L);
   p->o_uvu = take(4 * L);
-  p->max_partials = (int64_t)(L / (embc::kSumChunk / 2) + 2);
+  // the general path has at most 2 chunks per 65 lookups, a small call one per 8
+  p->max_partials = (int64_t)std::max(L / (embc::kSumChunk / 2) + 2, std::min(L, (size_t)embc::kSmallLookups) / 8 + 2);
   p->o_partial = take((size_t)p->max_partials * c->dim * 4);
   p->o_span = take((size_t)p->max_partials * 8);
   p->o_ubig = take(4 * (L + 1));
-  p->max_big = (int64_t)(L / (embc::kBlockAbove + 1) + 1);
+  p->max_big = (int64_t)(L / embc::kBlockAbove + 2);
   {
     const int64_t nb = embc::kBlockFloats / c->dim;
     p->max_nblk = (int32_t)((c->max_batch + nb - 1) / nb);
@@ -225,6 +226,7 @@ int plan_config(const emb_cache_config* c, Plan* p) {
   p->o_tabf = take(4 * (size_t)(T + 1));
   p->o_src = take(4 * L);
   p->o_ctr = take(8 * embc::kNCounters);
+  p->o_tabi = take(sizeof(embc::TabInfo) * (size_t)T);
   p->ws_bytes = o;
   return EMB_OK;
 }
@@ -239,6 +241,7 @@ struct emb_cache {
   embc::Work work;
   uint64_t step = 0;
   int key_bits = 1;
+  int local_passes = 1;  // digit passes of the largest table's local keys
   int seg_passes = 0;  // digit passes of the per-table sort, 0 = sort the whole key
   // measurement: event pairs around the row-update kernel of the last kTimedCalls calls
   static constexpr int kTimedCalls = 64;
@@ -383,6 +386,7 @@ int create_impl(const emb_cache_config* cfg, void* state, size_t state_bytes, vo
     int64_t max_range = 1;
     for (int t = 0; t < cfg->num_tables; ++t) max_range = std::max(max_range, p.key_base[t + 1] - p.key_base[t]);
     const int seg = (bit_length((uint64_t)max_range) + 7) / 8;
+    h->local_passes = seg;
     h->seg_passes = seg < (h->key_bits + 7) / 8 ? seg : 0;
   }
 
@@ -456,6 +460,7 @@ int create_impl(const emb_cache_config* cfg, void* state, size_t state_bytes, vo
   w.tab_first = reinterpret_cast<int32_t*>(wb + p.o_tabf);
   w.fwd_src = reinterpret_cast<int32_t*>(wb + p.o_src);
   w.ctr = reinterpret_cast<unsigned long long*>(wb + p.o_ctr);
+  w.tab_info = reinterpret_cast<embc::TabInfo*>(wb + p.o_tabi);
   w.max_indices = cfg->max_indices;
   w.max_partials = p.max_partials;
 
@@ -519,8 +524,12 @@ int emb_cache_backward_update(emb_cache_t h, const int32_t* indices, int64_t num
   const bool decay = h->cfg.policy == EMB_LFU && K > 0 && h->step > 0 && h->step % (uint64_t)K == 0;
   const hipEvent_t* tev = nullptr;
   if (h->timing) tev = &h->tev[2 * (h->timed % emb_cache::kTimedCalls)];
-  const hipError_t e = embc::launch_backward(h->dev, h->work, indices, num_indices, offsets, batch, grad_out,
-                                             h->step, h->key_bits, h->seg_passes, decay, tev, h->side, S(stream));
+  const bool small = embc::small_call(num_indices, batch, h->cfg.num_tables);
+  const hipError_t e =
+      small ? embc::launch_backward_small(h->dev, h->work, indices, num_indices, offsets, batch, grad_out, h->step,
+                                          h->local_passes, decay, tev, S(stream))
+            : embc::launch_backward(h->dev, h->work, indices, num_indices, offsets, batch, grad_out, h->step,
+                                    h->key_bits, h->seg_passes, decay, tev, h->side, S(stream));
   if (e != hipSuccess) return EMB_EHIP;
   if (h->timing) h->timed += 1;
   h->step += 1;

@@ -1,0 +1,163 @@
+"""GPU parity at the sizes where a call changes its route: the three-launch step of small calls
+(one workgroup per table: 1024 to 16384 keys in LDS, more in memory) up to 65536 lookups and
+512 tables, the general step above, and the forward in one kernel below 2^18 lookups.  Every
+piece of state, statistic and pooled output equals the oracle's bit for bit."""
+import numpy as np
+import pytest
+
+from common import custom_cfg
+from paper_2010_11305_amd import workload
+from parity import compare_state, log, make_pair, step_both
+
+pytestmark = pytest.mark.gpu
+
+LRU = dict(policy="lru", assoc=8, optimizer="adagrad", rounding="stochastic", bits=4, sb_fp16=True)
+LFU = dict(policy="lfu", assoc=4, lfu_decay_interval=2, optimizer="adagrad", bits=8)
+DIRECT = dict(policy="lru", assoc=1, bits=16, rounding="stochastic")
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    if not t.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2010_11305_amd import emb_cache
+    emb_cache.load()
+    return t
+
+
+def steps(torch, cfg, n=2, edit=None):
+    o, g = make_pair(cfg)
+    for k in range(n):
+        st = workload.make_step(cfg, k)
+        if edit:
+            edit(st, k)
+        step_both(o, g, cfg, st, torch)
+        compare_state(o, g, cfg)
+    return o, g
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1024, 1025, 2048, 2049, 4097, 8192, 8193, 16384, 16385, 32769, 65536, 65537])
+def test_lookups_of_one_table(torch, n):
+    """One table with n one-lookup bags: the edges of the key counts per thread, of the LDS
+    sort, of the tiles in memory and of the small call; rows past 8, 64 and 512 lookups."""
+    cfg = custom_cfg(rows=[70_000], batch=n, pooling=("fixed", 1), zipf=1.2, cache_fraction=0.02, **LRU)
+    log(f"one table, {n} lookups")
+    steps(torch, cfg)
+
+
+@pytest.mark.parametrize("dim", [16, 32, 64, 128, 256])
+@pytest.mark.parametrize("knobs", ["lru", "lfu", "direct"])
+def test_small_step_widths(torch, dim, knobs):
+    """Three tables (one without lookups in the second step, one with a single set), ragged
+    and empty bags, invalid indices; rows on both sides of 8, 64 and 512 lookups."""
+    kw = {"lru": LRU, "lfu": LFU, "direct": DIRECT}[knobs]
+    cfg = custom_cfg(rows=[900, 40, 30_000], dim=dim, batch=700, pooling=("uniform", 0, 9), zipf=1.3,
+                     cache_fraction=0.05, **kw)
+    log(f"small step d{dim} {knobs}")
+
+    def edit(st, k):
+        if k == 1:
+            off = st["offsets"]
+            B = cfg["batch"]
+            a, b = off[B], off[2 * B]
+            st["indices"] = np.delete(st["indices"], np.s_[a:b])
+            off[B:2 * B + 1] = a
+            off[2 * B + 1:] -= b - a
+        st["indices"][::97] = -5
+        st["indices"][3::101] = 30_000
+
+    o, g = steps(torch, cfg, 3, edit)
+    from paper_2010_11305_amd import emb_cache as ec
+    assert g.check() == ec.EMB_EINDEX
+
+
+@pytest.mark.parametrize("assoc,policy", [(1, "lru"), (2, "lru"), (16, "lru"), (32, "lfu"), (64, "lru"), (64, "lfu"), (1, "lfu")])
+def test_sets_with_more_rows_than_lanes(torch, assoc, policy):
+    """One set per table and up to 600 touched rows in it: candidates and victims beyond one
+    row per lane."""
+    cfg = custom_cfg(rows=[600, 97], batch=900, pooling=("uniform", 1, 4), zipf=1.05, cache_fraction=1e-6,
+                     assoc=assoc, policy=policy)
+    log(f"one set, {assoc} ways, {policy}")
+    steps(torch, cfg, 4)
+
+
+def test_one_table_holds_all_lookups(torch):
+    """Four tables of which one has 40000 lookups (sorted in memory, by tiles) in three bags of
+    many repeats, the others a few."""
+    cfg = custom_cfg(rows=[5000, 300, 7000, 9], batch=3, dim=32, **LRU)
+    o, g = make_pair(cfg, max_indices=50_000)
+    rng = np.random.default_rng(5)
+    for k in range(2):
+        sizes = np.array([[2, 0, 3], [15_000, 5, 25_000], [0, 1, 0], [4, 4, 4]])
+        off = np.concatenate([[0], np.cumsum(sizes.ravel())]).astype(np.int32)
+        idx = np.concatenate([(rng.zipf(1.3, size=s.sum()) % n).astype(np.int32) for s, n in zip(sizes, cfg["rows"])])
+        grad = rng.standard_normal((3, 4, 32)).astype(np.float32)
+        step_both(o, g, cfg, {"indices": idx, "offsets": off, "batch": 3, "grad": grad}, torch)
+        compare_state(o, g, cfg)
+
+
+@pytest.mark.parametrize("T", [512, 513])
+def test_table_count_edges(torch, T):
+    cfg = custom_cfg(rows=[50 + 7 * (t % 11) for t in range(T)], batch=8, pooling=("uniform", 0, 4), cache_fraction=0.1,
+                     assoc=4, zipf=1.1)
+    log(f"{T} tables")
+    steps(torch, cfg)
+
+
+GENERAL = {
+    "lru": dict(rows=[40_000, 5, 61_001, 300], dim=16, batch=4001, pooling=("uniform", 0, 12), zipf=1.2,
+                cache_fraction=0.05, **LRU),
+    "lfu": dict(rows=[40_000, 5, 61_001, 300], dim=64, batch=4001, pooling=("uniform", 0, 12), zipf=1.2,
+                cache_fraction=0.05, **LFU),
+    "direct_d128": dict(rows=[20_000], dim=128, batch=9000, pooling=("poisson", 9), zipf=1.2, cache_fraction=0.05,
+                        **DIRECT),
+    "assoc64_d256": dict(rows=[30_000, 77], dim=256, batch=3500, pooling=("poisson", 10), zipf=1.2, cache_fraction=0.05,
+                         assoc=64, bits=8),
+    "no_cache": dict(rows=[5000, 900], dim=32, batch=5000, pooling=("poisson", 8), zipf=1.2, cache_fraction=0.0),
+    # whole-key sort of many small tables; more than 64 tables in a workgroup's range
+    "many_tables": dict(rows=[50 + 7 * (t % 11) for t in range(600)], dim=16, batch=48, pooling=("uniform", 0, 5),
+                        cache_fraction=0.1, assoc=2, zipf=1.1),
+    # both sides of the one-kernel forward
+    "forward_below": dict(rows=[30_000, 700], dim=32, batch=13_107, pooling=("fixed", 9), zipf=1.2, cache_fraction=0.05,
+                          assoc=16, policy="lru"),
+    "forward_above": dict(rows=[30_000, 700], dim=32, batch=13_107, pooling=("fixed", 11), zipf=1.2, cache_fraction=0.05,
+                          assoc=16, policy="lru"),
+}
+
+
+@pytest.mark.parametrize("case", list(GENERAL))
+def test_general_step(torch, case):
+    """Calls past the small limits, with invalid indices in the second step."""
+    cfg = custom_cfg(**GENERAL[case])
+    log(f"general step {case}")
+
+    def edit(st, k):
+        if k == 1:
+            st["indices"][::997] = -1
+
+    steps(torch, cfg, 2, edit)
+
+
+@pytest.mark.parametrize("batch", [64, 20_000])
+def test_malformed_offsets_reject_the_call(torch, batch):
+    """Bad offsets of one table (decreasing; past the lookups; negative) in a small and a
+    general call: no table changes, the statistics read 0, on a step with an LFU decay too."""
+    from paper_2010_11305_amd import emb_cache as ec
+    cfg = custom_cfg(rows=[500, 300, 900], batch=batch, pooling=("fixed", 2), policy="lfu", lfu_decay_interval=1, assoc=4)
+    o, g = steps(torch, cfg, 1)
+    for where, value in ((batch + 5, -3), (2 * batch + 1, 10**9), (batch + 7, 1)):
+        st = workload.make_step(cfg, 1)
+        off = st["offsets"].copy()
+        off[where] = value
+        dev = [torch.from_numpy(x).cuda() for x in (st["indices"], off, st["grad"])]
+        g.backward_update(dev[0], dev[1], batch, dev[2])
+        o.backward_update(st["indices"], off, batch, st["grad"])
+        torch.cuda.synchronize()
+        assert g.check() == ec.EMB_EINDEX
+        for t in range(3):
+            s = g.stats(t)
+            assert all(s[f] == 0 for f in ec.STAT_NAMES[2:10]) and s["invalid_bwd"] == 0
+        compare_state(o, g, cfg)
+    step_both(o, g, cfg, workload.make_step(cfg, 2), torch)
+    compare_state(o, g, cfg)
