@@ -122,22 +122,22 @@ struct Dev {
 };
 
 // Small calls (k_small.hip): three launches, in which one workgroup per table sorts the table's
-// lookups.  Measured steps (us), small against general path: 26 tables of 2048 lookups 47
-// and 208, 400 of 160: 60 and 286, 16 of 3600: 79 and 230, 4 of 15000 (128 columns) 180 and
-// 266, one of 16384: 92 and 166, but one of 32768: 213 and 164 -- past 16384 lookups in a
-// table its workgroup sorts in memory.  The host knows the number of lookups of all tables
-// together, so the line is drawn at 16384 per table on average and 65536 in all; a call whose
-// lookups are nearly all in one table is then at most 0.1 ms slower than on the general path.
+// lookups.  Measured steps (us), small against mid path and against the general one: 26
+// tables of 2048 lookups 47, 94 and 208, 16 of 3600: 79, 102 and 230, one of 8192: 62, 92
+// and 169; past 8192 lookups in a table its workgroup sorts in memory (one table of 20000:
+// 159, 98 and 161).  The host knows the number of lookups of all tables together, so the
+// line is drawn at 8192 per table on average and 65536 in all (nearly all of those in one
+// of many tables: 0.38 ms, 0.30 on the general path before the mid path was there).
 constexpr int64_t kSmallLookups = 65536;
-constexpr int64_t kSmallPerTable = 16384;
+constexpr int64_t kSmallPerTable = 8192;
 constexpr int kSmallTables = 512;
 constexpr int32_t kSmallBags = 65536;
 constexpr bool small_call(int64_t L, int32_t B, int T) {
   return L <= kSmallLookups && L <= kSmallPerTable * T && B <= kSmallBags && T <= kSmallTables;
 }
 
-// The lists of one table in a small call, at offsets that follow from pos: unique rows and
-// sets from pos on, chunk sums from pos/8, big rows from pos/512.
+// The lists of one table in a small or mid call, at offsets that follow from pos: unique rows
+// and sets from pos on, chunk sums from pos/8 (pos/16 in a mid call), big rows from pos/512.
 struct TabInfo {
   uint32_t pos;     // its first lookup
   uint32_t rows;    // unique rows
@@ -145,8 +145,26 @@ struct TabInfo {
   uint32_t chunks;  // chunk sums
   uint32_t big;     // rows with more than kBlockAbove lookups
   uint32_t bad;     // its offsets were rejected
-  uint32_t pad[2];
+  uint32_t skipped; // lookups out of range (mid calls)
+  uint32_t valid;   // the others (mid calls)
 };
+
+// Calls of moderate size (launch_mid_front, then as a small call): below 2M lookups, or 8M of
+// at most 2^18 per table.  Measured steps (us), mid against general path: 26 tables of 8192
+// lookups 125 and 247, 10 of 40000: 168 and 290, one of 1.2M (128 columns) 435 and 455, 100
+// of 30000: 592 and 960, 100 of 61000 (LFU) 1303 and 1438, 10 of 246000: 587 and 625; but 10
+// of 491000: 1040 and 917, 100 of 123000: 2396 and 2114 -- with that many lookups per table
+// the general path's gradient sums from LDS-staged bag blocks and its second stream win.
+constexpr int64_t kMidLookups = 1 << 21, kMidLookupsMost = 1 << 23, kMidPerTable = 1 << 18;
+constexpr int kMidWaves = 8192;  // waves of 64 bags from which on the expansion takes 64 bags per wave
+constexpr bool mid_call(int64_t L, int32_t B, int T) {
+  return L > 0 && B > 0 && T <= kSmallTables &&
+         (L < kMidLookups || (L < kMidLookupsMost && L <= kMidPerTable * T));
+}
+// Rows of up to this many lookups are summed by the update itself, and a chunk of the others
+// has at least one more; the chunk sums of a table start at pos >> shift.
+constexpr uint32_t kSmallDirect = 8, kMidDirect = 16;
+constexpr int kSmallChunkShift = 3, kMidChunkShift = 4;
 
 // Per-call temporaries carved from the caller's workspace buffer.
 struct Work {
@@ -233,10 +251,15 @@ hipError_t launch_backward(const Dev& d, const Work& w, const int32_t* idx, int6
                            int32_t B, const float* grad, uint64_t step, int key_bits, int seg_passes, bool decay,
                            const hipEvent_t* update_events, const SideStream& side, hipStream_t s);
 
-// The same step for a small_call; passes: 8-bit digits of the largest table's local keys.
+// The same step for a small_call or (mid) a mid_call; passes: 8-bit digits of the largest table's local keys.
 hipError_t launch_backward_small(const Dev& d, const Work& w, const int32_t* idx, int64_t L, const int32_t* off,
                                  int32_t B, const float* grad, uint64_t step, int passes, bool decay,
-                                 const hipEvent_t* update_events, hipStream_t s);
+                                 const hipEvent_t* update_events, hipStream_t s, bool mid);
+
+// A mid_call: the sorted lookups and the tables' lists up to k_mid_rows, which the step's
+// remaining launches complete; *keys and *sval are the sorted pairs.
+hipError_t launch_mid_front(const Dev& d, const Work& w, const int32_t* idx, int64_t L, const int32_t* off, int32_t B,
+                            int passes, int group, const uint32_t** keys, const uint32_t** sval, hipStream_t s);
 
 size_t sort_status_words(int64_t n, int T);
 size_t sort_seg_words(int T);

@@ -1,11 +1,13 @@
-// Backward + sparse update of a small call (at most kSmallLookups lookups) in three
-// launches instead of about 27:
+// Backward + sparse update of a small call in three launches instead of about 27 (and the
+// launches of a mid call after its sort, k_sort.hip):
 //   k_front    one workgroup per table: offsets checked, lookups expanded, sorted in LDS, the
 //              unique rows, touched sets and gradient-sum jobs listed
 //   k_decide   replacement decisions per touched set (the probe included) and, by other
 //              workgroups of the same launch, the gradient sums of rows with many lookups
 //   k_apply    per unique row: merged gradient, fetch, optimizer, write-back; an insert
 //              first writes the resident it displaces back to T
+// (k_fold before k_apply when a row's block sums are many; k_mid_rows in place of the last part
+// of k_front in a mid call).
 // A launch that waits for the one before costs about 5 us on the device whatever it does, so
 // a step of a few thousand lookups is as long as its number of launches.  Tables are
 // independent and a table's unique rows, sets and jobs are listed at offsets that follow
@@ -23,12 +25,10 @@ namespace embc {
 constexpr int kFrontThreads = 1024;
 constexpr int kFrontWaves = kFrontThreads / 64;
 // Keys per thread of a table sorted in LDS, at most (8 bytes each with their values), and of
-// a tile of a larger one, whose pairs are in memory.
-constexpr int kFrontItems = 8, kFrontItemsWide = 16;
+// a tile of a larger one, whose pairs are in memory.  (With 16 the kernel spills registers;
+// scratch memory alone adds 3 to 14 us to its launch.)
+constexpr int kFrontItems = 8;
 constexpr int kFrontTile = kFrontThreads * kFrontItems;
-// Rows of up to kSumDirect lookups are summed by k_apply; longer ones, in chunks of
-// kSumChunk up to kBlockAbove lookups and by bag blocks above, by k_decide.
-constexpr uint32_t kSumDirect = 8;
 
 // ---- block scans of k_front ------------------------------------------------------------------
 template <typename T, typename Op>
@@ -68,30 +68,22 @@ __device__ __forceinline__ uint64_t same_digit(uint32_t d, bool valid) {
   return m;
 }
 
-template <int MAXI>
 struct FrontLds {
-  uint32_t key[kFrontThreads * MAXI];
-  uint32_t val[kFrontThreads * MAXI];
+  uint32_t key[kFrontTile];
+  uint32_t val[kFrontTile];
   uint32_t cnt[kFrontWaves][256];  // digit counts of each wave, then its offsets
   uint32_t dpre[256];
   uint32_t hist[kMaxPasses][256];  // a table in memory: digit counts of every pass, then the digits' ends
   unsigned long long scan[kFrontWaves];
-  uint32_t rows[MAXI * kFrontWaves], sets[MAXI * kFrontWaves];  // starts per run of 64 keys
+  uint32_t rows[kFrontItems * kFrontWaves], sets[kFrontItems * kFrontWaves];  // starts per run of 64 keys
   uint32_t n_bad, n_chunk, n_big;
 };
-
-// With 16 keys per thread the items are kept apart in the schedule: interleaved, their lane
-// masks spilled registers to scratch memory.
-template <int ITEMS>
-__device__ __forceinline__ void front_fence() {
-  if constexpr (ITEMS > kFrontItems) __builtin_amdgcn_sched_barrier(0);
-}
 
 // Ranks of ITEMS keys per thread (wave-major order: item i of wave w is key w*64*ITEMS +
 // i*64 + lane) among the wave's keys of the same digit; leaves the wave's digit counts in
 // S.cnt.  A wave's LDS operations complete in order, so its row needs no barrier.
-template <int ITEMS, typename LDS>
-__device__ __forceinline__ void front_rank(LDS& S, const uint32_t (&k)[ITEMS], uint32_t n, int shift,
+template <int ITEMS>
+__device__ __forceinline__ void front_rank(FrontLds& S, const uint32_t (&k)[ITEMS], uint32_t n, int shift,
                                            uint32_t (&rank)[ITEMS]) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   for (int i = lane; i < 256; i += 64) S.cnt[wv][i] = 0;
@@ -106,14 +98,12 @@ __device__ __forceinline__ void front_rank(LDS& S, const uint32_t (&k)[ITEMS], u
     if (valid && before == 0) old = atomicAdd(&S.cnt[wv][d], (uint32_t)__popcll(peers));
     const int first = valid ? (int)__builtin_ctzll(peers) : lane;
     rank[i] = __shfl(old, first) + before;
-    front_fence<ITEMS>();
   }
 }
 
 // After a barrier: the waves' digit counts become offsets inside their digit (S.cnt), and
 // returns, in threads below 256, the digit's total.
-template <typename LDS>
-__device__ __forceinline__ uint32_t front_wave_offsets(LDS& S) {
+__device__ __forceinline__ uint32_t front_wave_offsets(FrontLds& S) {
   uint32_t run = 0;
   if (threadIdx.x < 256) {
 #pragma unroll
@@ -128,8 +118,8 @@ __device__ __forceinline__ uint32_t front_wave_offsets(LDS& S) {
 
 // Stable sort of n <= 1024*ITEMS pairs (k, v) in wave-major order by `passes` 8-bit digits;
 // the sorted keys are left in S.key, the values in vout.
-template <int ITEMS, typename LDS>
-__device__ __forceinline__ void front_sort(LDS& S, uint32_t (&k)[ITEMS], uint32_t (&v)[ITEMS], uint32_t n,
+template <int ITEMS>
+__device__ __forceinline__ void front_sort(FrontLds& S, uint32_t (&k)[ITEMS], uint32_t (&v)[ITEMS], uint32_t n,
                                            int passes, uint32_t* __restrict__ vout) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   for (int p = 0; p < passes; ++p) {
@@ -179,8 +169,8 @@ struct FrontTab {
 // at or before it: by ballot inside a run of 64, then from the run before, then from the
 // waves before.  `carry` is the mark before the tile, and is moved past it.  Bags
 // [b0, b1) hold every bag that starts in the tile.
-template <int ITEMS, typename LDS>
-__device__ __forceinline__ bool front_expand(LDS& S, const FrontTab& f, const TableDesc& td, uint32_t t0,
+template <int ITEMS>
+__device__ __forceinline__ bool front_expand(FrontLds& S, const FrontTab& f, const TableDesc& td, uint32_t t0,
                                              uint32_t m, int b0, int b1, uint32_t& carry, uint32_t (&k)[ITEMS],
                                              uint32_t (&v)[ITEMS]) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -221,7 +211,6 @@ __device__ __forceinline__ bool front_expand(LDS& S, const FrontTab& f, const Ta
     const uint32_t near = __shfl(x, at ? 63 - (int)__clzll((unsigned long long)at) : 0);
     v[i] = at ? near : run;
     if (marks) run = __shfl(x, 63 - (int)__clzll((unsigned long long)marks));
-    front_fence<ITEMS>();
   }
   uint32_t* last = reinterpret_cast<uint32_t*>(S.scan);
   if (lane == 0) last[wv] = run;
@@ -247,7 +236,6 @@ __device__ __forceinline__ bool front_expand(LDS& S, const FrontTab& f, const Ta
     } else if (e < m) {
       ++n_bad;
     }
-    front_fence<ITEMS>();
   }
   if (n_bad) atomicAdd(&S.n_bad, n_bad);
   __syncthreads();
@@ -258,8 +246,8 @@ __device__ __forceinline__ bool front_expand(LDS& S, const FrontTab& f, const Ta
 // predecessor starts a row (first[u]: where), one of another set starts a set.  A run of 64
 // keys is one ballot, and a start's rank is its run's offset plus the starts before it in
 // the run.
-template <int ITEMS, typename LDS>
-__device__ __forceinline__ void front_unique(LDS& S, const Work& w, const TableDesc& td, const uint32_t* sk,
+template <int ITEMS>
+__device__ __forceinline__ void front_unique(FrontLds& S, const Work& w, const TableDesc& td, const uint32_t* sk,
                                              uint32_t P0, uint32_t t0, uint32_t m, uint32_t* first, uint32_t& nU,
                                              uint32_t& nS) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -274,7 +262,6 @@ __device__ __forceinline__ void front_unique(LDS& S, const Work& w, const TableD
       row = key != prev;
       set = row && (t0 + e == 0 || div_by(key, td.by_Q) != div_by(prev, td.by_Q));
     }
-    front_fence<ITEMS>();
     const uint64_t br = __ballot(row), bs = __ballot(set);
     if (lane == 0) {
       S.rows[wv * ITEMS + i] = (uint32_t)__popcll(br);
@@ -306,7 +293,6 @@ __device__ __forceinline__ void front_unique(LDS& S, const Work& w, const TableD
       w.set_first[P0 + s] = P0 + u;
       w.nch[P0 + s] = div_by(sk[t0 + (uint32_t)(wv * 64 * ITEMS + i * 64 + lane)], td.by_Q);
     }
-    front_fence<ITEMS>();
   }
   nU += (uint32_t)tot;
   nS += (uint32_t)(tot >> 32);
@@ -314,8 +300,8 @@ __device__ __forceinline__ void front_unique(LDS& S, const Work& w, const TableD
 }
 
 // A table whose keys fit the LDS: true if an offset is bad.
-template <int ITEMS, typename LDS>
-__device__ __forceinline__ bool front_table(LDS& S, const Work& w, const FrontTab& f, const TableDesc& td,
+template <int ITEMS>
+__device__ __forceinline__ bool front_table(FrontLds& S, const Work& w, const FrontTab& f, const TableDesc& td,
                                             int passes, uint32_t& nU, uint32_t& nS) {
   uint32_t k[ITEMS], v[ITEMS], carry = 0;
   if (front_expand<ITEMS>(S, f, td, 0, f.n, 0, f.B, carry, k, v)) return true;
@@ -327,8 +313,7 @@ __device__ __forceinline__ bool front_table(LDS& S, const Work& w, const FrontTa
 // One radix pass of n pairs in memory, a tile of kFrontTile at a time; S.hist[pass] holds the
 // digit counts.  A tile goes through the LDS in digit order, so that it is written in runs
 // (scattered from the registers, one line per lane and store, a tile took 17 us).
-template <typename LDS>
-__device__ __forceinline__ void front_pass(LDS& S, const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
+__device__ __forceinline__ void front_pass(FrontLds& S, const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
                                            uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, uint32_t n,
                                            int pass) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, shift = 8 * pass;
@@ -380,8 +365,7 @@ __device__ __forceinline__ void front_pass(LDS& S, const uint32_t* __restrict__ 
 
 // A table with more keys than the LDS holds: a tile at a time, the pairs in memory, where the
 // passes alternate between the two buffers and end in B.
-template <typename LDS>
-__device__ __forceinline__ bool front_large(LDS& S, const Work& w, const FrontTab& f, const TableDesc& td,
+__device__ __forceinline__ bool front_large(FrontLds& S, const Work& w, const FrontTab& f, const TableDesc& td,
                                          int passes, uint32_t& nU, uint32_t& nS) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   uint32_t* ka = w.keysA + f.P0;
@@ -450,11 +434,10 @@ __device__ __forceinline__ bool front_large(LDS& S, const Work& w, const FrontTa
 // table's flag).  Its time at 2048 lookups is about a chain of 12 barriers and memory
 // round trips per digit pass and list, not bandwidth: one workgroup holds the keys in
 // LDS and registers from the expansion to the lists.
-template <int MAXI>
 __global__ __launch_bounds__(kFrontThreads) void k_front(Dev dv, Work w, const int32_t* __restrict__ idx, int64_t L,
                                                          const int32_t* __restrict__ off, int32_t B, int passes,
                                                          int group) {
-  __shared__ FrontLds<MAXI> S;
+  __shared__ FrontLds S;
   const int t = blockIdx.x, tid = threadIdx.x;
   const TableDesc td = dv.desc[t];
   {
@@ -473,20 +456,19 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(Dev dv, Work w, const i
   if (tid == 0) S.n_bad = S.n_chunk = S.n_big = 0;
   // expanded, sorted by the local key (a skipped lookup's digits are all 255, above every
   // valid key's, so skipped lookups end the table's run), unique rows and sets listed
-  const bool in_lds = n <= (uint32_t)(kFrontThreads * MAXI);
+  const bool in_lds = n <= (uint32_t)kFrontTile;
   uint32_t* vb = w.valsB + P0;
   uint32_t nU = 0, nS = 0;
   if (!bad) {
     if (n <= 1 * kFrontThreads) bad = front_table<1>(S, w, f, td, passes, nU, nS);
     else if (n <= 2 * kFrontThreads) bad = front_table<2>(S, w, f, td, passes, nU, nS);
     else if (n <= 4 * kFrontThreads) bad = front_table<4>(S, w, f, td, passes, nU, nS);
-    else if (n <= 8 * kFrontThreads) bad = front_table<8>(S, w, f, td, passes, nU, nS);
-    else if (in_lds) bad = front_table<MAXI>(S, w, f, td, passes, nU, nS);
+    else if (in_lds) bad = front_table<kFrontItems>(S, w, f, td, passes, nU, nS);
     else bad = front_large(S, w, f, td, passes, nU, nS);
   }
   if (bad) {
     if (tid == 0) {
-      w.tab_info[t] = TabInfo{0, 0, 0, 0, 0, 1, {0, 0}};
+      w.tab_info[t] = TabInfo{0, 0, 0, 0, 0, 1, 0, 0};
       atomicOr(dv.err, kErrOffsets);
     }
     return;
@@ -498,10 +480,10 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(Dev dv, Work w, const i
   __syncthreads();
 
   // ---- per unique row: the update's inputs, and the jobs of the gradient sums (their order
-  // inside a table does not matter).  A row of more than kSumDirect lookups has at most one
+  // inside a table does not matter).  A row of more than kSmallDirect lookups has at most one
   // chunk per 9 of them and a row of more than kBlockAbove is one per 513, so the jobs of a
   // table fit the 1/8 and 1/512 of its positions.
-  const uint32_t cbase = P0 >> 3, hbase = P0 >> 9;
+  const uint32_t cbase = P0 >> kSmallChunkShift, hbase = P0 >> 9;
   for (uint32_t i0 = tid; i0 < nU; i0 += 4 * kFrontThreads) {
     uint32_t s0[4], s1[4], bag[4];
 #pragma unroll
@@ -525,7 +507,7 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(Dev dv, Work w, const i
       if (c > kBlockAbove) {
         aux = hbase + atomicAdd(&S.n_big, 1u);
         w.big_rows[aux] = (int32_t)u;
-      } else if (c > kSumDirect) {
+      } else if (c > kSmallDirect) {
         const uint32_t nc = (c + kSumChunk - 1) / kSumChunk;
         aux = cbase + atomicAdd(&S.n_chunk, nc);
         for (uint32_t j = 0; j < nc; ++j) {
@@ -538,7 +520,7 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(Dev dv, Work w, const i
   }
   __syncthreads();
   if (tid == 0) {
-    w.tab_info[t] = TabInfo{P0, nU, nS, S.n_chunk, S.n_big, 0, {0, 0}};
+    w.tab_info[t] = TabInfo{P0, nU, nS, S.n_chunk, S.n_big, 0, n - nv, nv};
     unsigned long long* st = dv.stats + ((int64_t)t << dv.stat_shift) * kStatStride;
     st[kStBwdLookups] = nv;
     st[kStInvalidBwd] = n - nv;
@@ -598,6 +580,99 @@ __device__ __forceinline__ int tab_of(const TabPrefix& P, int T, uint32_t i) {
     if (P.pre[mid] <= i) lo = mid; else hi = mid;
   }
   return lo;
+}
+
+// ---- unique rows of a mid call -----------------------------------------------------------------
+// Per unique row: its row, lookups and first occurrence, and its gradient-sum jobs.  A
+// workgroup takes kMidRows rows; the jobs of the rows of one table are placed with one
+// addition per workgroup to the table's count (a workgroup across a table boundary adds
+// per row).
+constexpr int kMidRows = 1024;
+
+__global__ __launch_bounds__(256) void k_mid_rows(Dev dv, Work w, const uint32_t* __restrict__ sk,
+                                                  const uint32_t* __restrict__ sval) {
+  __shared__ TabPrefix P;
+  __shared__ unsigned long long part[4];
+  __shared__ uint32_t at_s[2];
+  if (!tab_prefix(P, w.tab_info, dv.T, [](const TabInfo& x) { return x.rows; })) return;
+  constexpr int PER = kMidRows / 256;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const uint32_t nU = P.pre[dv.T];
+  for (uint32_t r0 = blockIdx.x * (uint32_t)kMidRows; r0 < nU; r0 += gridDim.x * (uint32_t)kMidRows) {
+    const uint32_t rend = min(r0 + (uint32_t)kMidRows, nU);
+    const int ta = tab_of(P, dv.T, r0), tb = tab_of(P, dv.T, rend - 1);  // whole workgroup
+    uint32_t s0[PER], c[PER], key[PER], bag[PER];
+    int tt[PER];
+    unsigned long long jobs = 0;  // chunks | big rows << 32
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const uint32_t i = min(r0 + (uint32_t)(q * 256) + threadIdx.x, rend - 1);
+      tt[q] = ta == tb ? ta : tab_of(P, dv.T, i);
+      const TabInfo& ti = w.tab_info[tt[q]];
+      const uint32_t k = i - P.pre[tt[q]];
+      s0[q] = w.seg[ti.pos + k];
+      c[q] = (k + 1 < ti.rows ? w.seg[ti.pos + k + 1] : ti.pos + ti.valid) - s0[q];
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      key[q] = sk[s0[q]];
+      bag[q] = sval[s0[q]];
+      if (r0 + (uint32_t)(q * 256) + threadIdx.x >= rend) c[q] = 0;
+      jobs += c[q] > kBlockAbove ? (1ull << 32) : c[q] > kMidDirect ? (c[q] + kSumChunk - 1) / kSumChunk : 0u;
+    }
+    unsigned long long x = jobs;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned long long y = __shfl_up(x, o);
+      if (lane >= o) x += y;
+    }
+    __syncthreads();  // the previous round's part and at_s have been read
+    if (lane == 63) part[wv] = x;
+    __syncthreads();
+    unsigned long long pre = x - jobs, tot = 0;
+    for (int k = 0; k < 4; ++k) {
+      if (k < wv) pre += part[k];
+      tot += part[k];
+    }
+    if (ta == tb && threadIdx.x < 2) {
+      const uint32_t n = threadIdx.x == 0 ? (uint32_t)tot : (uint32_t)(tot >> 32);
+      uint32_t* count = threadIdx.x == 0 ? &w.tab_info[ta].chunks : &w.tab_info[ta].big;
+      at_s[threadIdx.x] = n ? atomicAdd(count, n) : 0u;
+    }
+    __syncthreads();
+    uint32_t chunk_at = ta == tb ? at_s[0] + (uint32_t)pre : 0u, big_at = ta == tb ? at_s[1] + (uint32_t)(pre >> 32) : 0u;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      if (c[q] == 0) continue;
+      const int t = tt[q];
+      const uint32_t pos = w.tab_info[t].pos;
+      const uint32_t u = pos + r0 + (uint32_t)(q * 256) + threadIdx.x - P.pre[t];
+      const TableDesc& td = dv.desc[t];
+      uint32_t r = key[q] - (uint32_t)td.key_base;
+      if (td.n_sets > 0) {
+        const uint32_t set = div_by(r, td.by_Q);
+        r = (r - set * (uint32_t)td.Q) * (uint32_t)td.n_sets + set;
+      }
+      uint32_t aux = 0;
+      if (c[q] > kBlockAbove) {
+        aux = (pos >> 9) + (ta == tb ? big_at++ : atomicAdd(&w.tab_info[t].big, 1u));
+        w.big_rows[aux] = (int32_t)u;
+      } else if (c[q] > kMidDirect) {
+        const uint32_t nc = (c[q] + kSumChunk - 1) / kSumChunk;
+        if (ta == tb) {
+          aux = (pos >> kMidChunkShift) + chunk_at;
+          chunk_at += nc;
+        } else {
+          aux = (pos >> kMidChunkShift) + atomicAdd(&w.tab_info[t].chunks, nc);
+        }
+        for (uint32_t j = 0; j < nc; ++j) {
+          const uint32_t a = s0[q] + j * (uint32_t)kSumChunk;
+          w.chunk_span[aux + j] = make_uint2(a, min(a + (uint32_t)kSumChunk, s0[q] + c[q]));
+        }
+      }
+      w.umeta[u] = make_uint4((uint32_t)td.row_base + r, aux, c[q] == 1 ? bag[q] : s0[q], c[q]);
+    }
+  }
 }
 
 // ---- decisions ---------------------------------------------------------------------------------
@@ -662,14 +737,36 @@ __device__ __forceinline__ void decide_sets(const Dev& dv, const Work& w, TabPre
     __builtin_amdgcn_wave_barrier();
     uint32_t M = 0, H = 0;
     int64_t last_miss = -1;        // the set's last missed row
-    unsigned long long mykey = 0;  // LFU: rank key of the lane's row, when the set's rows fit the group
-    uint4 next = w.umeta[min(u0 + l, u1 - 1)];
+    // LFU: the lane's four best rank keys so far (count, then the lower row; 0: none), and
+    // their rows; a lane that has given all four looks for the next in memory (sets of more
+    // than 4G rows).  Scanning every key of the set for every candidate, a set of 2000 rows
+    // took 100 us.
+    unsigned long long top[4] = {0, 0, 0, 0};
+    int32_t top_u[4] = {-1, -1, -1, -1};
+    const auto keep = [&](unsigned long long key, int32_t u) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (key > top[i]) {
+          const unsigned long long k1 = top[i];
+          const int32_t u1_ = top_u[i];
+          top[i] = key;
+          top_u[i] = u;
+          key = k1;
+          u = u1_;
+        }
+      }
+    };
+    // the rows are loaded two rounds ahead and their counts one (a set may have thousands)
+    uint4 next = w.umeta[min(u0 + l, u1 - 1)], next2 = w.umeta[min(u0 + G + l, u1 - 1)];
+    int32_t cnext = !lru ? dv.cnt[next.x] : 0;
     for (uint32_t c = u0; c < u1; c += G) {
       const uint32_t u = c + l;
       const bool act = u < u1;
       const uint4 meta = next;
-      next = w.umeta[min(u + G, u1 - 1)];
-      const int32_t cnt0 = !lru && act ? dv.cnt[meta.x] : 0;
+      const int32_t cnt0 = cnext;
+      next = next2;
+      next2 = w.umeta[min(u + 2 * G, u1 - 1)];
+      if (!lru && c + G < u1) cnext = dv.cnt[next.x];
       const int32_t r = (int32_t)(meta.x - (uint32_t)td.row_base);
       int way = -1;
       if (A >= 4) {
@@ -691,8 +788,9 @@ __device__ __forceinline__ void decide_sets(const Dev& dv, const Work& w, TabPre
           const int64_t cc = (int64_t)cnt0 + meta.w;
           cn = cc > 0x7FFFFFFF ? 0x7FFFFFFF : (int32_t)cc;
           dv.cnt[meta.x] = cn;
-          mykey = hit ? 0ull : ((unsigned long long)(uint32_t)cn << 32) | (uint32_t)~meta.x;
-          if (u1 - u0 > (uint32_t)G) w.ukey[u] = mykey;
+          const unsigned long long key = hit ? 0ull : ((unsigned long long)(uint32_t)cn << 32) | (uint32_t)~meta.x;
+          keep(key, (int32_t)u);
+          if (u1 - u0 > 4 * (uint32_t)G) w.ukey[u] = key;
         }
         if (hit) {
           L.hitu[gb + way] = (int32_t)u;
@@ -744,25 +842,10 @@ __device__ __forceinline__ void decide_sets(const Dev& dv, const Work& w, TabPre
       }
       int K = M < (uint32_t)A ? (int)M : A;
       if (!lru) {
-        if (u1 - u0 > (uint32_t)G) __threadfence_block();  // the keys of the group's other lanes
-        __builtin_amdgcn_wave_barrier();
-        unsigned long long prev = ~0ull;
-        int taken = 0;
+        int given = 0, taken = 0;
         for (int r = 0; r < K; ++r) {
-          unsigned long long best = 0;
-          int32_t bu = -1;
-          if (u1 - u0 > (uint32_t)G) {
-            for (uint32_t c = u0 + l; c < u1; c += G) {
-              const unsigned long long ky = w.ukey[c];
-              if (ky < prev && ky > best) {
-                best = ky;
-                bu = (int32_t)c;
-              }
-            }
-          } else if (mykey < prev && mykey > 0) {
-            best = mykey;
-            bu = (int32_t)(u0 + l);
-          }
+          unsigned long long best = top[0];
+          int32_t bu = top_u[0];
 #pragma unroll
           for (int o = G / 2; o >= 1; o >>= 1) {
             const unsigned long long ob = __shfl_xor(best, o, G);
@@ -778,7 +861,20 @@ __device__ __forceinline__ void decide_sets(const Dev& dv, const Work& w, TabPre
             L.cand_u[gb + r] = bu;
             L.cand_pv[gb + r] = cpv;
           }
-          prev = best;
+          if (top[0] == best) {  // the one lane that had it (keys are unique)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+              top[i] = top[i + 1];
+              top_u[i] = top_u[i + 1];
+            }
+            top[3] = 0;
+            if (++given % 4 == 0 && u1 - u0 > 4 * (uint32_t)G) {
+              for (uint32_t c = u0 + l; c < u1; c += G) {  // (its own rows' keys)
+                const unsigned long long key = w.ukey[c];
+                if (key < best) keep(key, (int32_t)c);
+              }
+            }
+          }
           taken = r + 1;
         }
         K = taken;
@@ -923,15 +1019,15 @@ __device__ __forceinline__ uint32_t first_of_bag(const uint32_t* __restrict__ sv
 
 template <int D>
 __device__ __forceinline__ void sum_jobs(const Dev& dv, const Work& w, TabPrefix& P, const float* __restrict__ grad,
-                                         int nblk, int nb_shift, int wg, int nwg) {
+                                         const uint32_t* __restrict__ sval, int nblk, int nb_shift, int cshift, int wg,
+                                         int nwg) {
   constexpr int GL = SumGeo<D>::GL, CL = SumGeo<D>::CL, GPB = 256 / GL;
   const int l = threadIdx.x & (GL - 1);
-  const uint32_t* sval = w.valsB;
   // chunks, then (big row, bag block) pairs
   const uint32_t nC = P.pre[dv.T];
   for (uint32_t c = (uint32_t)wg * GPB + threadIdx.x / GL; c < nC; c += (uint32_t)nwg * GPB) {
     const int t = tab_of(P, dv.T, c);
-    const uint32_t at = (w.tab_info[t].pos >> 3) + c - P.pre[t];
+    const uint32_t at = (w.tab_info[t].pos >> cshift) + c - P.pre[t];
     const uint2 sp = w.chunk_span[at];
     float acc[CL];
     sum_span<D>(sval, sp.x, sp.y, grad_rows<D>(grad, t, dv.T), l, acc);
@@ -971,8 +1067,9 @@ __device__ __forceinline__ void sum_jobs(const Dev& dv, const Work& w, TabPrefix
 // Workgroups below n_sum take the gradient sums (the longer chains, started first), the
 // others the sets.
 template <int D, int G>
-__global__ __launch_bounds__(256) void k_decide(Dev dv, Work w, const float* __restrict__ grad, uint32_t step, int nblk,
-                                                int nb_shift, int n_sum) {
+__global__ __launch_bounds__(256) void k_decide(Dev dv, Work w, const uint32_t* __restrict__ sval,
+                                                const float* __restrict__ grad, uint32_t step, int nblk, int nb_shift,
+                                                int cshift, int n_sum) {
   __shared__ TabPrefix P;
   if ((int)blockIdx.x < n_sum) {
     if (!tab_prefix(P, w.tab_info, dv.T, [](const TabInfo& x) { return x.chunks; })) {
@@ -986,7 +1083,7 @@ __global__ __launch_bounds__(256) void k_decide(Dev dv, Work w, const float* __r
       }
       return;
     }
-    sum_jobs<D>(dv, w, P, grad, nblk, nb_shift, (int)blockIdx.x, n_sum);
+    sum_jobs<D>(dv, w, P, grad, sval, nblk, nb_shift, cshift, (int)blockIdx.x, n_sum);
   } else {
     if (!tab_prefix(P, w.tab_info, dv.T, [](const TabInfo& x) { return x.sets; })) return;
     decide_sets<G>(dv, w, P, step, (int)blockIdx.x - n_sum, (int)gridDim.x - n_sum);
@@ -1018,22 +1115,64 @@ __device__ __forceinline__ void fold_flagged(const Work& w, uint32_t h, int nblk
   }
 }
 
+// Up to kFoldInline blocks a row's sums are folded by the update; more, by a launch of their
+// own, one workgroup per row: its waves bring kFoldRows block sums at a time to the LDS,
+// where one lane per column adds them in order into the row's first slot.
+constexpr int kFoldInline = 8;
+
+template <int D>
+__global__ __launch_bounds__(256) void k_fold(Dev dv, Work w, int nblk) {
+  constexpr int kFoldRows = D == 256 ? 32 : 64, LPW = D / 4, PER = kFoldRows * LPW / 256;
+  __shared__ TabPrefix P;
+  __shared__ f4w stage[kFoldRows * LPW];
+  if (!tab_prefix(P, w.tab_info, dv.T, [](const TabInfo& x) { return x.big; })) return;
+  const float* sf = reinterpret_cast<const float*>(stage);
+  const uint32_t n = P.pre[dv.T];
+  for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const int t = tab_of(P, dv.T, i);
+    const uint32_t h = (w.tab_info[t].pos >> 9) + i - P.pre[t];
+    const uint32_t* fl = w.bbound + (int64_t)h * bound_stride(w.max_nblk);
+    float* bp = w.bpart + (int64_t)h * w.max_nblk * D;
+    float acc = -0.0f;
+    for (int k0 = 0; k0 < nblk; k0 += kFoldRows) {
+      f4w v[PER];
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        // (a block without occurrences has no sum: -0, the identity of the addition)
+        const int e = q * 256 + (int)threadIdx.x, k = k0 + e / LPW;
+        v[q] = f4w{-0.0f, -0.0f, -0.0f, -0.0f};
+        if (k < nblk && fl[k]) v[q] = reinterpret_cast<const f4w*>(bp + (int64_t)k * D)[e % LPW];
+      }
+      __syncthreads();  // the sums of the rows before have been read
+#pragma unroll
+      for (int q = 0; q < PER; ++q) stage[q * 256 + threadIdx.x] = v[q];
+      __syncthreads();
+      if ((int)threadIdx.x < D) {
+#pragma unroll 8
+        for (int r = 0; r < kFoldRows; ++r) acc = acc + sf[r * D + threadIdx.x];
+      }
+    }
+    if ((int)threadIdx.x < D) bp[threadIdx.x] = acc;
+    __syncthreads();
+  }
+}
+
 // Merged gradient of a unique row (inputs m).
 template <int D>
-__device__ __forceinline__ void small_grad(const Work& w, const uint4& m, GradRows<D> gr, int nblk, int g,
-                                           float (&acc)[8]) {
+__device__ __forceinline__ void small_grad(const Work& w, const uint32_t* __restrict__ sval, uint32_t direct,
+                                           const uint4& m, GradRows<D> gr, int nblk, int g, float (&acc)[8]) {
   constexpr int U = 4;
   const uint32_t n = m.w;
   if (n == 1) {
     load_row<D>(gr.row(m.z), g, acc);
-  } else if (n <= kSumDirect) {
+  } else if (n <= direct) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = -0.0f;
     for (uint32_t j = 0; j < n; j += U) {
       uint32_t b[U];
       float x[U][8];
 #pragma unroll
-      for (int q = 0; q < U; ++q) b[q] = w.valsB[m.z + min(j + q, n - 1)];
+      for (int q = 0; q < U; ++q) b[q] = sval[m.z + min(j + q, n - 1)];
 #pragma unroll
       for (int q = 0; q < U; ++q) load_row<D>(gr.row(b[q]), g, x[q]);
 #pragma unroll
@@ -1043,8 +1182,10 @@ __device__ __forceinline__ void small_grad(const Work& w, const uint4& m, GradRo
     }
   } else if (n <= kBlockAbove) {
     fold_chunks<D>(w.partial, m.y, (n + kSumChunk - 1) / kSumChunk, g, acc);
-  } else {
+  } else if (nblk <= kFoldInline) {
     fold_flagged<D>(w, m.y, nblk, g, acc);
+  } else {
+    load_row<D>(w.bpart + (int64_t)m.y * w.max_nblk * D, g, acc);
   }
 }
 
@@ -1052,7 +1193,8 @@ __device__ __forceinline__ void small_grad(const Work& w, const uint4& m, GradRo
 // own update if it has one (LFU and direct-mapped caches: a row updated this step and then
 // displaced), writes it back to T and takes the way; a way is touched by one row alone.
 template <int D, int BITS, bool SB16>
-__global__ __launch_bounds__(256) void k_apply(Dev dv, Work w, const float* __restrict__ grad, uint32_t step, int nblk) {
+__global__ __launch_bounds__(256) void k_apply(Dev dv, Work w, const uint32_t* __restrict__ sval,
+                                               const float* __restrict__ grad, uint32_t step, int nblk, uint32_t direct) {
   __shared__ TabPrefix P;
   constexpr int LPR = Geo<D>::LPR, GPB = 256 / LPR;
   if (!tab_prefix(P, w.tab_info, dv.T, [](const TabInfo& x) { return x.rows; })) return;
@@ -1100,7 +1242,7 @@ __global__ __launch_bounds__(256) void k_apply(Dev dv, Work w, const float* __re
         const float Gv = dv.optimizer ? dv.acc_slot[slot] : 0.0f;
         if (vu >= 0) {
           float gv[8];
-          small_grad<D>(w, w.umeta[vu], gtab, nblk, g, gv);
+          small_grad<D>(w, sval, direct, w.umeta[vu], gtab, nblk, g, gv);
           apply_optimizer<D>(dv, xv, gv, vacc, g, Gv);
         } else if (dv.optimizer && g == 0) {
           *vacc = Gv;
@@ -1108,7 +1250,7 @@ __global__ __launch_bounds__(256) void k_apply(Dev dv, Work w, const float* __re
         quantize_store<D, BITS, SB16>(xv, g, vrec, sr, dv.seed, step, (uint32_t)t, (uint32_t)vrow);
       }
     }
-    small_grad<D>(w, m, gtab, nblk, g, gr);
+    small_grad<D>(w, sval, direct, m, gtab, nblk, g, gr);
     if (!hit) {
       float sc, bi;
       decode_sb<SB16>(sbw, sc, bi);
@@ -1139,40 +1281,46 @@ __global__ __launch_bounds__(256) void k_decay_small(int32_t* __restrict__ cnt, 
 
 hipError_t launch_backward_small(const Dev& d, const Work& w, const int32_t* idx, int64_t L, const int32_t* off,
                                  int32_t B, const float* grad, uint64_t step64, int passes, bool decay,
-                                 const hipEvent_t* update_events, hipStream_t s) {
+                                 const hipEvent_t* update_events, hipStream_t s, bool mid) {
   const uint32_t step = (uint32_t)step64;
   const int G = d.assoc <= 16 ? 16 : d.assoc <= 32 ? 32 : 64;
   const int nb_shift = __builtin_ctz((unsigned)(kBlockFloats / d.dim));
   const int nblk = (int)(((int64_t)B + (kBlockFloats / d.dim) - 1) >> nb_shift);
-  if (nblk > w.max_nblk || d.T > kSmallTables || L > kSmallLookups) return hipErrorInvalidValue;
-  // 16 keys per thread where the tables hold more than 8192 lookups on average (one table of
-  // 16384: 66 us, 113 with the pairs in memory); the other kernel needs no scratch memory
-  // (2048 lookups per table: 18 us against 22) and sorts the odd larger table in memory
-  const auto front = [&](auto kernel) {
-    kernel<<<(unsigned)d.T, kFrontThreads, 0, s>>>(d, w, idx, L, off, B, passes, G);
-  };
-  if (L > (int64_t)d.T * kFrontTile) front(k_front<kFrontItemsWide>);
-  else front(k_front<kFrontItems>);
+  if (nblk > w.max_nblk || !(mid ? mid_call(L, B, d.T) : small_call(L, B, d.T))) return hipErrorInvalidValue;
+  const uint32_t* sval = w.valsB;
+  if (mid) {
+    const uint32_t* sk = nullptr;
+    const hipError_t e = launch_mid_front(d, w, idx, L, off, B, passes, G, &sk, &sval, s);
+    if (e != hipSuccess) return e;
+    const unsigned rounds = (unsigned)std::min<int64_t>((L + kMidRows - 1) / kMidRows, 1024);
+    k_mid_rows<<<rounds, 256, 0, s>>>(d, w, sk, sval);
+  } else {
+    k_front<<<(unsigned)d.T, kFrontThreads, 0, s>>>(d, w, idx, L, off, B, passes, G);
+  }
+  const uint32_t direct = mid ? kMidDirect : kSmallDirect;
+  const int cshift = mid ? kMidChunkShift : kSmallChunkShift;
   if (decay && d.cnt) k_decay_small<<<grid_for(d.total_rows), 256, 0, s>>>(d.cnt, d.total_rows, w.tab_info, d.T);
   return dispatch_row(d.dim, d.bits, d.sb16, [&]<int D, int BITS, bool SB16>() -> hipError_t {
-    // a set or a row per lookup, a chunk per kSumDirect + 1 at most
+    // a set or a row per lookup, a chunk per direct + 1 at most
     const auto blocks = [](int64_t items, int per, int64_t cap) {
       return (int)std::max<int64_t>(1, std::min<int64_t>((items + per - 1) / per, cap));
     };
-    const int n_sum = blocks(L / (kSumDirect + 1) + 1, 256 / SumGeo<D>::GL, 512);
+    const int n_sum = blocks(L / (direct + 1) + 1, 256 / SumGeo<D>::GL, mid ? 1536 : 512);
     const int n_set = blocks(L, 256 / G, 1024);
     const auto decide = [&](auto kernel) {
-      kernel<<<(unsigned)(n_sum + n_set), 256, 0, s>>>(d, w, grad, step, nblk, nb_shift, n_sum);
+      kernel<<<(unsigned)(n_sum + n_set), 256, 0, s>>>(d, w, sval, grad, step, nblk, nb_shift, cshift, n_sum);
     };
     if (G == 16) decide(k_decide<D, 16>);
     else if (G == 32) decide(k_decide<D, 32>);
     else decide(k_decide<D, 64>);
+    if (nblk > kFoldInline && L > (int64_t)kBlockAbove)
+      k_fold<D><<<(unsigned)blocks(L / kBlockAbove, 1, 1024), 256, 0, s>>>(d, w, nblk);
     if (update_events) {
       const hipError_t e = hipEventRecord(update_events[0], s);
       if (e != hipSuccess) return e;
     }
     const int64_t cap = resident_grid(reinterpret_cast<const void*>(k_apply<D, BITS, SB16>));
-    k_apply<D, BITS, SB16><<<(unsigned)blocks(L, 256 / Geo<D>::LPR, cap), 256, 0, s>>>(d, w, grad, step, nblk);
+    k_apply<D, BITS, SB16><<<(unsigned)blocks(L, 256 / Geo<D>::LPR, cap), 256, 0, s>>>(d, w, sval, grad, step, nblk, direct);
     if (update_events) {
       const hipError_t e = hipEventRecord(update_events[1], s);
       if (e != hipSuccess) return e;

@@ -6,6 +6,8 @@
 //                  per pass with decoupled look-back
 //   scans          3-phase exclusive prefix sums (u32 / u64)
 //   k_uniq_*       unique-row and touched-set lists (first occurrence of each row / set)
+#include <algorithm>
+
 #include "embc_device.h"
 #include "embc_dispatch.h"
 #include "embc_sort.h"
@@ -318,6 +320,18 @@ __device__ __forceinline__ int seg_of_tile(const uint32_t* tbase, int T, uint32_
   return lo;
 }
 
+// The same by a whole wave, 64 tables per round of loads.
+__device__ __forceinline__ int seg_of_tile_wave(const uint32_t* tbase, int T, uint32_t tile) {
+  int lo = 0;
+  for (int hi = T; hi - lo > 1;) {
+    const int step = (hi - lo + 63) / 64, c = lo + (int)(threadIdx.x & 63) * step;
+    const uint64_t le = __ballot(c == lo || (c < hi && tbase[c] <= tile));
+    lo += (63 - (int)__clzll((unsigned long long)le)) * step;
+    hi = min(hi, lo + step);
+  }
+  return lo;
+}
+
 // Digit of a key in a pass of the segmented mode: the local key's, or 255 when skipped.
 __device__ __forceinline__ uint32_t seg_digit(uint32_t key, uint32_t kb, int shift) {
   return key == kKeyInvalid ? 255u : ((key - kb) >> shift) & 255u;
@@ -438,7 +452,10 @@ __global__ __launch_bounds__(256) void k_seg_scan(SegSort sg, int passes, int64_
 // until none is left (the pass that only runs when some key was skipped: when none
 // was, it ends after one read of the flag per workgroup).  Either way a look-back only
 // waits on tiles whose workgroups took their ticket earlier and are running.
-constexpr int kModeWhole = 0, kModeSeg = 1, kModeSkipped = 2;
+// kModeRuns is kModeSeg for calls of moderate size: the digit runs' starts are scanned from
+// the counts by every tile itself, which saves a launch, and nothing is done when the
+// offsets were rejected (`only_if`, then a flag that stops the pass).
+constexpr int kModeWhole = 0, kModeSeg = 1, kModeSkipped = 2, kModeRuns = 3;
 
 template <int MODE, bool LOOP>
 __global__ __launch_bounds__(kRadixThreads) void k_sort_pass(const uint32_t* __restrict__ kin,
@@ -458,7 +475,8 @@ __global__ __launch_bounds__(kRadixThreads) void k_sort_pass(const uint32_t* __r
   __shared__ uint32_t lds4[4];
   __shared__ uint32_t tile_s;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  constexpr bool SEG = MODE == kModeSeg;
+  constexpr bool SEG = MODE == kModeSeg || MODE == kModeRuns;
+  if (MODE == kModeRuns && *only_if != 0) return;
   const int64_t ntiles = SEG ? (int64_t)sg.tbase[T]
                              : (only_if == nullptr || *only_if != 0) ? (n + kRadixTile - 1) / kRadixTile : 0;
   for (;;) {
@@ -472,14 +490,14 @@ __global__ __launch_bounds__(kRadixThreads) void k_sort_pass(const uint32_t* __r
     int64_t tfirst = 0, lo = tile * kRadixTile, hi = min<int64_t>(n, lo + kRadixTile);
     uint32_t kb = 0;
     if (SEG) {
-      t = seg_of_tile(sg.tbase, T, (uint32_t)tile);
+      t = MODE == kModeRuns ? seg_of_tile_wave(sg.tbase, T, (uint32_t)tile) : seg_of_tile(sg.tbase, T, (uint32_t)tile);
       tfirst = sg.tbase[t];
       lo = sg.pos[t] + (tile - tfirst) * kRadixTile;
       hi = min<int64_t>(sg.pos[t + 1], lo + kRadixTile);
       kb = (uint32_t)key_base[t];
     }
     const auto digit = [&](uint32_t key) -> uint32_t {
-      if constexpr (MODE == kModeSeg) return seg_digit(key, kb, shift);
+      if constexpr (SEG) return seg_digit(key, kb, shift);
       else if constexpr (MODE == kModeSkipped) return key == kKeyInvalid ? 1u : 0u;
       else return (key >> shift) & 255u;
     };
@@ -545,7 +563,12 @@ __global__ __launch_bounds__(kRadixThreads) void k_sort_pass(const uint32_t* __r
       }
       uint32_t tot;
       dpre[d] = block_exclusive_scan<uint32_t>(run, lds4, tot);
-      goff[d] = (SEG ? sg.base[((int64_t)t * kMaxPasses + pass) * 256 + d] : gbase[d]) + excl;
+      if constexpr (MODE == kModeRuns) {
+        const uint32_t runs = block_exclusive_scan<uint32_t>(sg.hist[((int64_t)t * kMaxPasses + pass) * 256 + d], lds4, tot);
+        goff[d] = sg.pos[t] + runs + excl;
+      } else {
+        goff[d] = (SEG ? sg.base[((int64_t)t * kMaxPasses + pass) * 256 + d] : gbase[d]) + excl;
+      }
     }
     __syncthreads();
 #pragma unroll
@@ -674,6 +697,302 @@ hipError_t sort_pairs_segmented(uint32_t* kA, uint32_t* vA, uint32_t* kB, uint32
                                                             ss.status[passes & 1], ss.tickets + passes, nullptr,
                                                             256 * nb, err, SegSort{}, nullptr, 0, 0, any_skipped);
   k_copy_pairs<<<grid_for(n, 2048), 256, 0, s>>>(ko, vo, kr, vr, n, any_skipped);
+  return hipGetLastError();
+}
+
+// ---- calls of moderate size ------------------------------------------------------------------
+// The front of the step for a mid_call: the tables' segments are sorted by their local keys as
+// in the segmented mode, and the unique rows, sets and jobs of a table are listed at
+// offsets that follow from its first position (TabInfo), where the launches of a small call
+// take them up.  Eight launches and no pass over all tables: a scan over the unique rows
+// of all tables, a pass that moves skipped lookups behind every table's and the lists made from
+// it cost twelve more, some 5 us each.
+//   k_mid_begin    statistics, counts and tickets zeroed; offsets checked (a flag per
+//                  workgroup); segments, first tiles
+//   k_mid_expand   lookups -> (local key, bag), digit counts per table
+//   k_sort_pass    the digit passes
+//   k_mid_count    per tile of sorted keys: rows and sets that start in it
+//   k_mid_write    their first occurrences, at the table's offset plus the tiles before
+//   k_mid_rows     per unique row: the update's inputs, the jobs of the gradient sums
+__global__ __launch_bounds__(256) void k_mid_begin(Dev dv, Work w, const int32_t* __restrict__ off, int32_t B, int64_t L,
+                                                   SegSort sg, uint32_t* __restrict__ tickets,
+                                                   uint32_t* __restrict__ flags) {
+  __shared__ uint32_t lds4[4];
+  zero_stats(dv, kStBwdLookups, kStHitEvictions);
+  zero_stats(dv, kStInvalidBwd, kStInvalidBwd);
+  const int T = dv.T;
+  const int64_t stride = (int64_t)gridDim.x * 256, tid = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  for (int64_t i = tid; i < (int64_t)T * kMaxPasses * 256; i += stride) sg.hist[i] = 0;
+  bool bad = false;
+  for (int64_t i = tid; i < (int64_t)T * B; i += stride) {
+    const int64_t a = off[i], b = off[i + 1];
+    bad |= a < 0 || b < a || b > L;
+  }
+  bad = __syncthreads_or(bad) != 0;
+  if (threadIdx.x == 0) {
+    flags[blockIdx.x] = bad ? 1u : 0u;
+    if (bad) atomicOr(dv.err, kErrOffsets);
+  }
+  if (blockIdx.x != 0) return;
+  if (threadIdx.x < kMaxPasses) tickets[threadIdx.x] = 0;
+  // (rejected offsets may give anything here; nothing uses it then)
+  const auto start = [&](int t) -> int64_t { return min<int64_t>(max<int64_t>(off[(int64_t)t * B], 0), L); };
+  uint32_t run = 0;
+  for (int t0 = 0; t0 <= T; t0 += 256) {
+    const int t = t0 + (int)threadIdx.x;
+    uint32_t tiles = 0;
+    int64_t p = 0;
+    if (t <= T) {
+      p = start(t);
+      if (t < T) tiles = (uint32_t)((max<int64_t>(start(t + 1) - p, 0) + kRadixTile - 1) / kRadixTile);
+    }
+    uint32_t tot;
+    const uint32_t ex = block_exclusive_scan<uint32_t>(tiles, lds4, tot);
+    if (t <= T) {
+      sg.pos[t] = (uint32_t)p;
+      sg.tbase[t] = run + ex;
+      if (t < T) w.tab_info[t] = TabInfo{(uint32_t)p, 0, 0, 0, 0, 0, 0, 0};
+    }
+    run += tot;
+  }
+}
+
+// WAVES waves of BPW bags each per workgroup (256 bags of one table): 64 bags per wave when
+// there are many waves anyway, 16 when there are not (a wave goes through its bags' lookups
+// 128 at a time).  A workgroup across a table boundary would add the second table's counts to
+// memory one by one, on hot digits one after another: 42 us at 0.49M lookups instead of 14.
+template <int WAVES, int BPW>
+__global__ __launch_bounds__(WAVES * 64) void k_mid_expand(Dev dv, Work w, const int32_t* __restrict__ idx, int64_t L,
+                                                           const int32_t* __restrict__ off, int32_t B,
+                                                           DivConst per_table, const uint32_t* __restrict__ flags, int nflags,
+                                                           uint32_t* __restrict__ bad_out, ExpandHist eh) {
+  constexpr int NT = WAVES * 64;
+  __shared__ uint32_t h[kMaxPasses * 256];
+  __shared__ uint32_t skipped_s;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  {
+    bool bad = false;
+    for (int i = threadIdx.x; i < nflags; i += NT) bad |= flags[i] != 0;
+    bad = __syncthreads_or(bad) != 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      *bad_out = bad ? 1u : 0u;
+      if (bad) w.tab_info[0].bad = 1;
+    }
+    if (bad) return;
+  }
+  const int64_t stride = (int64_t)gridDim.x * NT;
+  for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < eh.status_words; i += stride) eh.status[i] = 0;
+  const int t = (int)div_by(blockIdx.x, per_table);
+  const int32_t wg_bag = (int32_t)(blockIdx.x - (uint32_t)t * per_table.d) * (WAVES * BPW);
+  const TableDesc td = dv.desc[t];
+  const int32_t* offt = off + (int64_t)t * B;
+  for (int i = threadIdx.x; i < eh.passes * 256; i += NT) h[i] = 0;
+  if (threadIdx.x == 0) skipped_s = 0;
+  __syncthreads();
+  uint32_t n_skip = 0;
+  const int32_t bag0 = wg_bag + wv * BPW;
+  if (bag0 < B) {
+    const int32_t lastbag = min(bag0 + BPW, B);
+    const int64_t st = lane < BPW && bag0 + lane < B ? (int64_t)offt[bag0 + lane] : L;
+    const int64_t P0 = offt[bag0], P1 = offt[lastbag];
+    const auto handle = [&](int64_t p, int32_t r, int j) {
+      uint32_t key = kKeyInvalid, local = kKeyInvalid;
+      if (r >= 0 && (int64_t)r < td.N) {
+        local = (uint32_t)r;
+        if (td.n_sets > 0) {
+          const uint32_t q = div_by((uint32_t)r, td.by_sets);
+          local = ((uint32_t)r - q * (uint32_t)td.n_sets) * (uint32_t)td.Q + q;
+        }
+        key = (uint32_t)td.key_base + local;
+      } else {
+        ++n_skip;
+      }
+      w.keysA[p] = key;
+      w.valsA[p] = (uint32_t)(bag0 + j);
+      for (int q = 0; q < eh.passes; ++q) atomicAdd(&h[q * 256 + ((local >> (8 * q)) & 255u)], 1u);
+    };
+    for (int64_t pc = P0; pc < P1; pc += 128) {
+      const int64_t pA = pc + lane, pB = pc + 64 + lane;
+      const bool inA = pA < P1, inB = pB < P1;
+      const int32_t rA = inA ? idx[pA] : 0;
+      const int32_t rB = inB ? idx[pB] : 0;
+      int jA = 0, jB = 0;
+#pragma unroll
+      for (int step = BPW / 2; step >= 1; step >>= 1) {
+        const int64_t sA = __shfl(st, jA + step);
+        const int64_t sB = __shfl(st, jB + step);
+        if (sA <= pA) jA += step;
+        if (sB <= pB) jB += step;
+      }
+      if (inA) handle(pA, rA, jA);
+      if (inB) handle(pB, rB, jB);
+    }
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) n_skip += __shfl_xor(n_skip, o);
+  if (lane == 0 && n_skip) atomicAdd(&skipped_s, n_skip);
+  __syncthreads();
+  uint32_t* ht = eh.hist + (int64_t)t * kMaxPasses * 256;
+  for (int i = threadIdx.x; i < eh.passes * 256; i += NT) {
+    const uint32_t c = h[i];
+    if (c) atomicAdd(&ht[i], c);
+  }
+  if (threadIdx.x == 0 && skipped_s) atomicAdd(&w.tab_info[t].skipped, skipped_s);
+}
+
+// The sorted keys of tile `tile`: its table, its first position and the end of its valid keys.
+struct MidTile {
+  int t;
+  uint32_t lo, hi, tfirst, pos, nv;
+};
+__device__ __forceinline__ MidTile mid_tile(const Work& w, const SegSort& sg, int T, uint32_t tile) {
+  MidTile m;
+  m.t = seg_of_tile_wave(sg.tbase, T, tile);
+  m.tfirst = sg.tbase[m.t];
+  m.pos = sg.pos[m.t];
+  const uint32_t n = sg.pos[m.t + 1] - m.pos;
+  m.nv = n - w.tab_info[m.t].skipped;  // skipped lookups end the segment
+  m.lo = min(m.pos + (tile - m.tfirst) * (uint32_t)kRadixTile, m.pos + m.nv);
+  m.hi = min(m.lo + (uint32_t)kRadixTile, m.pos + m.nv);
+  return m;
+}
+
+// Which of the thread's 16 keys (wave-major runs of 64) start a row or a set.
+__device__ __forceinline__ void mid_starts(const Dev& dv, const TableDesc& td, const uint32_t* __restrict__ sk,
+                                           const MidTile& m, uint32_t& rows, uint32_t& sets) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  rows = sets = 0;
+  uint32_t k[kRadixItems], q[kRadixItems];
+#pragma unroll
+  for (int i = 0; i < kRadixItems; ++i) {
+    const uint32_t e = m.lo + (uint32_t)(wv * 64 * kRadixItems + i * 64 + lane);
+    k[i] = e < m.hi ? sk[e] : 0u;
+    q[i] = e < m.hi && e > m.pos ? sk[e - 1] : kKeyInvalid;
+  }
+  const uint32_t kb = (uint32_t)td.key_base;
+#pragma unroll
+  for (int i = 0; i < kRadixItems; ++i) {
+    const uint32_t e = m.lo + (uint32_t)(wv * 64 * kRadixItems + i * 64 + lane);
+    const bool row = e < m.hi && k[i] != q[i];
+    const bool set = row && (e == m.pos || div_by(k[i] - kb, td.by_Q) != div_by(q[i] - kb, td.by_Q));
+    rows |= (row ? 1u : 0u) << i;
+    sets |= (set ? 1u : 0u) << i;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_mid_count(Dev dv, Work w, const uint32_t* __restrict__ sk, SegSort sg,
+                                                   const uint32_t* __restrict__ bad) {
+  __shared__ unsigned long long lds4[4];
+  if (*bad != 0 || blockIdx.x >= sg.tbase[dv.T]) return;
+  const MidTile m = mid_tile(w, sg, dv.T, blockIdx.x);
+  uint32_t rows, sets;
+  mid_starts(dv, dv.desc[m.t], sk, m, rows, sets);
+  unsigned long long tot;
+  block_exclusive_scan<unsigned long long>(
+      (unsigned long long)__popc(rows) | ((unsigned long long)__popc(sets) << 32), lds4, tot);
+  if (threadIdx.x == 0) w.tile_cnt[blockIdx.x] = tot;
+}
+
+__global__ __launch_bounds__(256) void k_mid_write(Dev dv, Work w, const uint32_t* __restrict__ sk, SegSort sg,
+                                                   const uint32_t* __restrict__ bad, int group) {
+  __shared__ unsigned long long lds4[4];
+  __shared__ uint32_t run_rows[4 * kRadixItems], run_sets[4 * kRadixItems];
+  if (*bad != 0 || blockIdx.x >= sg.tbase[dv.T]) return;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const MidTile m = mid_tile(w, sg, dv.T, blockIdx.x);
+  const TableDesc td = dv.desc[m.t];
+  // the rows and sets of the table's tiles before this one
+  unsigned long long c = 0, before;
+  for (uint32_t j = m.tfirst + threadIdx.x; j < blockIdx.x; j += 256) c += w.tile_cnt[j];
+  block_exclusive_scan<unsigned long long>(c, lds4, before);
+  uint32_t rows, sets;
+  mid_starts(dv, td, sk, m, rows, sets);
+#pragma unroll
+  for (int i = 0; i < kRadixItems; ++i) {
+    const uint64_t br = __ballot((rows >> i) & 1u), bs = __ballot((sets >> i) & 1u);
+    if (lane == 0) {
+      run_rows[wv * kRadixItems + i] = (uint32_t)__popcll(br);
+      run_sets[wv * kRadixItems + i] = (uint32_t)__popcll(bs);
+    }
+  }
+  __syncthreads();
+  unsigned long long tot;
+  const int r = threadIdx.x;
+  const unsigned long long ex = block_exclusive_scan<unsigned long long>(
+      r < 4 * kRadixItems ? (unsigned long long)run_rows[r] | ((unsigned long long)run_sets[r] << 32) : 0ull, lds4, tot);
+  if (r < 4 * kRadixItems) {
+    run_rows[r] = (uint32_t)(before + ex);
+    run_sets[r] = (uint32_t)((before + ex) >> 32);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kRadixItems; ++i) {
+    const bool row = (rows >> i) & 1u, set = (sets >> i) & 1u;
+    const uint64_t br = __ballot(row), bs = __ballot(set);
+    const uint32_t e = m.lo + (uint32_t)(wv * 64 * kRadixItems + i * 64 + lane);
+    const uint32_t u = m.pos + run_rows[wv * kRadixItems + i] + (uint32_t)__popcll(br & lanemask_lt());
+    if (row) w.seg[u] = e;
+    if (set && td.n_sets > 0) {
+      const uint32_t s = m.pos + run_sets[wv * kRadixItems + i] + (uint32_t)__popcll(bs & lanemask_lt());
+      w.set_first[s] = u;
+      w.nch[s] = div_by(sk[e] - (uint32_t)td.key_base, td.by_Q);
+    }
+  }
+  // the table's last tile knows its totals
+  if (threadIdx.x == 0 && blockIdx.x + 1 == sg.tbase[m.t + 1]) {
+    const uint32_t nU = (uint32_t)(before + tot);
+    TabInfo& ti = w.tab_info[m.t];
+    ti.rows = nU;
+    ti.sets = td.n_sets > 0 ? (uint32_t)((before + tot) >> 32) : (nU + (uint32_t)group - 1) / (uint32_t)group;
+    ti.valid = m.nv;
+    unsigned long long* st = dv.stats + ((int64_t)m.t << dv.stat_shift) * kStatStride;
+    st[kStBwdLookups] = m.nv;
+    st[kStInvalidBwd] = ti.skipped;
+    st[kStUnique] = nU;
+    if (td.n_sets == 0) st[kStBypasses] = nU;
+    if (ti.skipped) atomicOr(dv.err, kErrIndex);
+  }
+}
+
+hipError_t launch_mid_front(const Dev& d, const Work& w, const int32_t* idx, int64_t L, const int32_t* off, int32_t B,
+                            int passes, int group, const uint32_t** keys, const uint32_t** sval, hipStream_t s) {
+  if (L <= 0 || passes < 1 || passes > kMaxPasses || L > (int64_t)kStCount || d.T < 1 || B < 1)
+    return hipErrorInvalidValue;
+  const int64_t nbags = (int64_t)d.T * B;
+  const SortScratch ss{w.sort_small, w.sort_small + kMaxPasses * 256, w.sort_small + 2 * kMaxPasses * 256,
+                       {w.sort_status[0], w.sort_status[1]}};
+  const size_t TT = (size_t)d.T * kMaxPasses * 256;
+  const SegSort sg{w.sort_seg, w.sort_seg + (d.T + 1), w.sort_seg + 2 * (d.T + 1), w.sort_seg + 2 * (d.T + 1) + TT};
+  uint32_t* flags = ss.ghist;        // one per workgroup of k_mid_begin
+  uint32_t* bad_flag = ss.gbase;
+  const unsigned nflags = grid_for(std::max<int64_t>(nbags / 4, (int64_t)TT / 4), 256);
+  const int64_t tiles = (L + kRadixTile - 1) / kRadixTile + d.T;
+  ExpandHist eh;
+  eh.hist = sg.hist;
+  eh.key_base = d.key_base;
+  eh.status = ss.status[0];
+  eh.status_words = 256 * tiles;
+  eh.passes = passes;
+  k_mid_begin<<<nflags, 256, 0, s>>>(d, w, off, B, L, sg, ss.tickets, flags);
+  const DivConst per_table = div_const((uint32_t)(((int64_t)B + 255) / 256));
+  const unsigned wgs = per_table.d * (unsigned)d.T;
+  if (nbags < (int64_t)64 * kMidWaves)
+    k_mid_expand<16, 16><<<wgs, 1024, 0, s>>>(d, w, idx, L, off, B, per_table, flags, (int)nflags, bad_flag, eh);
+  else
+    k_mid_expand<4, 64><<<wgs, 256, 0, s>>>(d, w, idx, L, off, B, per_table, flags, (int)nflags, bad_flag, eh);
+  uint32_t *ki = w.keysA, *vi = w.valsA, *ko = w.keysB, *vo = w.valsB;
+  for (int p = 0; p < passes; ++p) {
+    uint32_t* next = p + 1 < passes ? ss.status[(p + 1) & 1] : nullptr;
+    k_sort_pass<kModeRuns, false><<<(unsigned)tiles, kRadixThreads, 0, s>>>(
+        ki, vi, ko, vo, L, 8 * p, nullptr, ss.status[p & 1], ss.tickets + p, next, eh.status_words, d.err, sg, d.key_base,
+        d.T, p, bad_flag);
+    std::swap(ki, ko);
+    std::swap(vi, vo);
+  }
+  k_mid_count<<<(unsigned)tiles, 256, 0, s>>>(d, w, ki, sg, bad_flag);
+  k_mid_write<<<(unsigned)tiles, 256, 0, s>>>(d, w, ki, sg, bad_flag, group);
+  *sval = vi;
+  *keys = ki;
   return hipGetLastError();
 }
 

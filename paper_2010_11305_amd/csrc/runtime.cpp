@@ -193,7 +193,7 @@ int plan_config(const emb_cache_config* c, Plan* p) {
   p->o_sst1 = take(4 * embc::sort_status_words((int64_t)L, T));
   p->o_sseg = take(4 * embc::sort_seg_words(T));
   p->o_part = take(8 * embc::scan_partial_words((int64_t)L + 256 * 64));
-  p->o_tcnt = take(8 * embc::uniq_tile_words((int64_t)L));
+  p->o_tcnt = take(8 * (embc::uniq_tile_words((int64_t)L) + (size_t)T));  // a mid call's tiles end with their table
   p->o_tpre = take(8 * embc::uniq_tile_words((int64_t)L));
   p->o_tthr = take(8 * 256 * embc::uniq_tile_words((int64_t)L));
   p->o_uk = take(4 * L);
@@ -210,8 +210,11 @@ int plan_config(const emb_cache_config* c, Plan* p) {
   p->o_cbase = take(4 * (L + 1));
   p->o_uvrow = take(4 * L);
   p->o_uvu = take(4 * L);
-  // the general path has at most 2 chunks per 65 lookups, a small call one per 8
-  p->max_partials = (int64_t)std::max(L / (embc::kSumChunk / 2) + 2, std::min(L, (size_t)embc::kSmallLookups) / 8 + 2);
+  // the general path has at most 2 chunks per 65 lookups, a small call one per 8, a mid call
+  // one per 16
+  p->max_partials = (int64_t)std::max({L / (embc::kSumChunk / 2) + 2,
+                                       (std::min(L, (size_t)embc::kSmallLookups) >> embc::kSmallChunkShift) + 2,
+                                       (std::min(L, (size_t)embc::kMidLookupsMost) >> embc::kMidChunkShift) + 2});
   p->o_partial = take((size_t)p->max_partials * c->dim * 4);
   p->o_span = take((size_t)p->max_partials * 8);
   p->o_ubig = take(4 * (L + 1));
@@ -525,9 +528,11 @@ int emb_cache_backward_update(emb_cache_t h, const int32_t* indices, int64_t num
   const hipEvent_t* tev = nullptr;
   if (h->timing) tev = &h->tev[2 * (h->timed % emb_cache::kTimedCalls)];
   const bool small = embc::small_call(num_indices, batch, h->cfg.num_tables);
+  const bool mid = !small && embc::mid_call(num_indices, batch, h->cfg.num_tables);
   const hipError_t e =
-      small ? embc::launch_backward_small(h->dev, h->work, indices, num_indices, offsets, batch, grad_out, h->step,
-                                          h->local_passes, decay, tev, S(stream))
+      small || mid
+            ? embc::launch_backward_small(h->dev, h->work, indices, num_indices, offsets, batch, grad_out, h->step,
+                                          h->local_passes, decay, tev, S(stream), mid)
             : embc::launch_backward(h->dev, h->work, indices, num_indices, offsets, batch, grad_out, h->step,
                                     h->key_bits, h->seg_passes, decay, tev, h->side, S(stream));
   if (e != hipSuccess) return EMB_EHIP;

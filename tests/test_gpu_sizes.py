@@ -1,7 +1,8 @@
 """GPU parity at the sizes where a call changes its route: the three-launch step of small calls
-(one workgroup per table: 1024 to 16384 keys in LDS, more in memory) up to 65536 lookups and
-512 tables, the general step above, and the forward in one kernel below 2^18 lookups.  Every
-piece of state, statistic and pooled output equals the oracle's bit for bit."""
+(one workgroup per table: 1024 to 8192 keys in LDS, more in memory) up to 65536 lookups, 8192
+per table on average and 512 tables; the mid step up to 2M lookups; the general step above
+either; and the forward in one kernel below 2^18 lookups.  Every piece of state, statistic
+and pooled output equals the oracle's bit for bit."""
 import numpy as np
 import pytest
 
@@ -37,7 +38,7 @@ def steps(torch, cfg, n=2, edit=None):
     return o, g
 
 
-@pytest.mark.parametrize("n", [1, 63, 64, 65, 1024, 1025, 2048, 2049, 4097, 8192, 8193, 16384, 16385, 32769, 65536, 65537])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1024, 1025, 2048, 2049, 4097, 8191, 8192, 8193, 16384, 20481, 65537])
 def test_lookups_of_one_table(torch, n):
     """One table with n one-lookup bags: the edges of the key counts per thread, of the LDS
     sort, of the tiles in memory and of the small call; rows past 8, 64 and 512 lookups."""
@@ -82,17 +83,18 @@ def test_sets_with_more_rows_than_lanes(torch, assoc, policy):
     steps(torch, cfg, 4)
 
 
-def test_one_table_holds_all_lookups(torch):
-    """Four tables of which one has 40000 lookups (sorted in memory, by tiles) in three bags of
-    many repeats, the others a few."""
-    cfg = custom_cfg(rows=[5000, 300, 7000, 9], batch=3, dim=32, **LRU)
+@pytest.mark.parametrize("T", [4, 6])
+def test_one_table_holds_all_lookups(torch, T):
+    """Six tables of which one has 40000 lookups (a small call, sorted in memory by tiles; the
+    same from four tables on is a mid call) in three bags of many repeats, the others a few."""
+    cfg = custom_cfg(rows=[5000, 300, 7000, 9, 20, 20][:T], batch=3, dim=32, **LRU)
     o, g = make_pair(cfg, max_indices=50_000)
     rng = np.random.default_rng(5)
     for k in range(2):
-        sizes = np.array([[2, 0, 3], [15_000, 5, 25_000], [0, 1, 0], [4, 4, 4]])
+        sizes = np.array([[2, 0, 3], [15_000, 5, 25_000], [0, 1, 0], [4, 4, 4], [0, 0, 0], [1, 2, 3]][:T])
         off = np.concatenate([[0], np.cumsum(sizes.ravel())]).astype(np.int32)
         idx = np.concatenate([(rng.zipf(1.3, size=s.sum()) % n).astype(np.int32) for s, n in zip(sizes, cfg["rows"])])
-        grad = rng.standard_normal((3, 4, 32)).astype(np.float32)
+        grad = rng.standard_normal((3, T, 32)).astype(np.float32)
         step_both(o, g, cfg, {"indices": idx, "offsets": off, "batch": 3, "grad": grad}, torch)
         compare_state(o, g, cfg)
 
@@ -105,7 +107,7 @@ def test_table_count_edges(torch, T):
     steps(torch, cfg)
 
 
-GENERAL = {
+MID = {
     "lru": dict(rows=[40_000, 5, 61_001, 300], dim=16, batch=4001, pooling=("uniform", 0, 12), zipf=1.2,
                 cache_fraction=0.05, **LRU),
     "lfu": dict(rows=[40_000, 5, 61_001, 300], dim=64, batch=4001, pooling=("uniform", 0, 12), zipf=1.2,
@@ -126,11 +128,11 @@ GENERAL = {
 }
 
 
-@pytest.mark.parametrize("case", list(GENERAL))
-def test_general_step(torch, case):
+@pytest.mark.parametrize("case", list(MID))
+def test_mid_step(torch, case):
     """Calls past the small limits, with invalid indices in the second step."""
-    cfg = custom_cfg(**GENERAL[case])
-    log(f"general step {case}")
+    cfg = custom_cfg(**MID[case])
+    log(f"mid step {case}")
 
     def edit(st, k):
         if k == 1:
@@ -139,10 +141,37 @@ def test_general_step(torch, case):
     steps(torch, cfg, 2, edit)
 
 
+@pytest.mark.parametrize("dim", [16, 32, 64, 128, 256])
+@pytest.mark.parametrize("knobs", ["lru", "lfu", "direct"])
+def test_general_step(torch, dim, knobs):
+    """513 tables, more than the small and mid steps take: whole-key and per-table sorts, rows
+    of up to 64, up to 512 and more lookups, invalid indices in the second step."""
+    kw = {"lru": LRU, "lfu": LFU, "direct": DIRECT}[knobs]
+    cfg = custom_cfg(rows=[30_000] + [40] * 512 if knobs != "lru" else [300] * 513, dim=dim, batch=64,
+                     pooling=("uniform", 0, 40), zipf=2.0, cache_fraction=0.1, **kw)
+    log(f"general step d{dim} {knobs}")
+
+    def edit(st, k):
+        if k == 1:
+            st["indices"][::997] = -1
+
+    idx, off = workload.make_indices(cfg, 0)
+    assert max(np.bincount(idx[off[t * 64]:off[(t + 1) * 64]]).max() for t in range(1, 5)) > 512
+    steps(torch, cfg, 2, edit)
+
+
+def test_mid_step_large_sets_and_folds(torch):
+    """LFU sets of more than 128 rows (a lane looks for its fifth candidate in memory) and rows
+    spread over more than 8 bag blocks, in one table."""
+    cfg = custom_cfg(rows=[4000], dim=256, batch=2500, pooling=("poisson", 30), zipf=1.1, cache_fraction=0.004,
+                     policy="lfu", assoc=16, bits=8)
+    steps(torch, cfg, 3)
+
+
 @pytest.mark.parametrize("batch", [64, 20_000])
 def test_malformed_offsets_reject_the_call(torch, batch):
     """Bad offsets of one table (decreasing; past the lookups; negative) in a small and a
-    general call: no table changes, the statistics read 0, on a step with an LFU decay too."""
+    mid call: no table changes, the statistics read 0, on a step with an LFU decay too."""
     from paper_2010_11305_amd import emb_cache as ec
     cfg = custom_cfg(rows=[500, 300, 900], batch=batch, pooling=("fixed", 2), policy="lfu", lfu_decay_interval=1, assoc=4)
     o, g = steps(torch, cfg, 1)
