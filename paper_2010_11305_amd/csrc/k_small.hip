@@ -583,23 +583,25 @@ __device__ __forceinline__ int tab_of(const TabPrefix& P, int T, uint32_t i) {
 }
 
 // ---- unique rows of a mid call -----------------------------------------------------------------
-// Per unique row: its row, lookups and first occurrence, and its gradient-sum jobs.  A
-// workgroup takes kMidRows rows; the jobs of the rows of one table are placed with one
+// Per unique row: its row, lookups and first occurrence, its gradient-sum jobs, and its probe
+// with the update of its priority (with one group of lanes per set doing these as in a small
+// call, an LFU set of 2000 rows took 90 us of a step of 222).  A
+// workgroup takes 256*PER rows (one per thread below 2^19 lookups, whose rows are few
+// workgroups' worth); the jobs of the rows of one table are placed with one
 // addition per workgroup to the table's count (a workgroup across a table boundary adds
 // per row).
-constexpr int kMidRows = 1024;
-
+template <int MAXA, int PER>
 __global__ __launch_bounds__(256) void k_mid_rows(Dev dv, Work w, const uint32_t* __restrict__ sk,
-                                                  const uint32_t* __restrict__ sval) {
+                                                  const uint32_t* __restrict__ sval, uint32_t step) {
   __shared__ TabPrefix P;
   __shared__ unsigned long long part[4];
   __shared__ uint32_t at_s[2];
   if (!tab_prefix(P, w.tab_info, dv.T, [](const TabInfo& x) { return x.rows; })) return;
-  constexpr int PER = kMidRows / 256;
+  constexpr uint32_t kRows = 256 * PER;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const uint32_t nU = P.pre[dv.T];
-  for (uint32_t r0 = blockIdx.x * (uint32_t)kMidRows; r0 < nU; r0 += gridDim.x * (uint32_t)kMidRows) {
-    const uint32_t rend = min(r0 + (uint32_t)kMidRows, nU);
+  for (uint32_t r0 = blockIdx.x * kRows; r0 < nU; r0 += gridDim.x * kRows) {
+    const uint32_t rend = min(r0 + kRows, nU);
     const int ta = tab_of(P, dv.T, r0), tb = tab_of(P, dv.T, rend - 1);  // whole workgroup
     uint32_t s0[PER], c[PER], key[PER], bag[PER];
     int tt[PER];
@@ -670,7 +672,19 @@ __global__ __launch_bounds__(256) void k_mid_rows(Dev dv, Work w, const uint32_t
           w.chunk_span[aux + j] = make_uint2(a, min(a + (uint32_t)kSumChunk, s0[q] + c[q]));
         }
       }
-      w.umeta[u] = make_uint4((uint32_t)td.row_base + r, aux, c[q] == 1 ? bag[q] : s0[q], c[q]);
+      const uint32_t grow = (uint32_t)td.row_base + r;
+      w.umeta[u] = make_uint4(grow, aux, c[q] == 1 ? bag[q] : s0[q], c[q]);
+      const int32_t slot = probe_slot<MAXA>(dv, td, (int32_t)r);
+      w.uslot[u] = slot;
+      w.uact[u] = slot >= 0 ? kActHitStay : kActBypass;
+      if (dv.policy == 0) {
+        if (slot >= 0) dv.ts[slot] = (int32_t)step;
+      } else {
+        const int64_t cc = (int64_t)dv.cnt[grow] + c[q];
+        const int32_t cn = cc > 0x7FFFFFFF ? 0x7FFFFFFF : (int32_t)cc;
+        dv.cnt[grow] = cn;
+        w.ukey[u] = slot >= 0 ? 0ull : ((unsigned long long)(uint32_t)cn << 32) | (uint32_t)~grow;
+      }
     }
   }
 }
@@ -680,8 +694,9 @@ __global__ __launch_bounds__(256) void k_mid_rows(Dev dv, Work w, const uint32_t
 // lane, and every row of the set is compared with all of them by a ballot, so the probe
 // needs no pass of its own; then the priorities are updated and the inserts and their
 // victims chosen as k_policy does.  The set's rows, tags, stamps and the counts of its rows
-// are touched by this group alone.
-template <int G>
+// are touched by this group alone.  PROBED: k_mid_rows has probed the rows and updated the
+// priorities.
+template <int G, bool PROBED>
 __device__ __forceinline__ void decide_sets(const Dev& dv, const Work& w, TabPrefix& P, uint32_t step, int wg, int nwg) {
   __shared__ PolicyLds lds_all[4];
   __shared__ int32_t hitc_all[4][64];  // LFU: the count of the row that hit way w
@@ -714,7 +729,7 @@ __device__ __forceinline__ void decide_sets(const Dev& dv, const Work& w, TabPre
     if (td.n_sets == 0) {
       // no cache: every row is written to T (their bypasses were counted with the lists)
       const uint32_t u = ti.pos + ((uint32_t)k - P.pre[t]) * G + l;
-      if (u < uend) {
+      if (!PROBED && u < uend) {
         w.uact[u] = kActBypass;
         if (!lru) {
           const uint4 m = w.umeta[u];
@@ -731,6 +746,7 @@ __device__ __forceinline__ void decide_sets(const Dev& dv, const Work& w, TabPre
     if (l < A) {
       tg = dv.tag[sbase + l];
       if (lru) vpv = dv.ts[sbase + l];
+      else if (PROBED && tg >= 0) vpv = dv.cnt[td.row_base + tg];
     }
     L.hitu[lane] = -1;
     tags[lane] = tg;
@@ -757,6 +773,35 @@ __device__ __forceinline__ void decide_sets(const Dev& dv, const Work& w, TabPre
       }
     };
     // the rows are loaded two rounds ahead and their counts one (a set may have thousands)
+    if constexpr (PROBED) {
+      const auto slot_at = [&](uint32_t u) { return w.uslot[min(u, u1 - 1)]; };
+      const auto key_at = [&](uint32_t u) { return lru ? 0ull : w.ukey[min(u, u1 - 1)]; };
+      int32_t sa = slot_at(u0 + l), sb = slot_at(u0 + G + l);
+      unsigned long long ka = key_at(u0 + l), kb = key_at(u0 + G + l);
+      for (uint32_t c = u0; c < u1; c += G) {
+        const uint32_t u = c + l;
+        const int32_t sl = sa;
+        const unsigned long long key = ka;
+        sa = sb;
+        ka = kb;
+        sb = slot_at(u + 2 * G);
+        kb = key_at(u + 2 * G);
+        const bool hit = u < u1 && sl >= 0, miss = u < u1 && sl < 0;
+        if (hit) L.hitu[gb + (int)(sl - sbase)] = (int32_t)u;
+        if (!lru && miss) keep(key, (int32_t)u);
+        const uint64_t mm = __ballot(miss) & gmask;
+        if (lru) {
+          const uint32_t rank = M + (uint32_t)__popcll(mm & below);
+          if (miss && rank < (uint32_t)A) {
+            L.cand_u[gb + rank] = (int32_t)u;
+            L.cand_pv[gb + rank] = (long long)step;
+          }
+          if (mm) last_miss = (int64_t)c + (63 - __clzll((unsigned long long)mm)) - gb;
+        }
+        M += (uint32_t)__popcll(mm);
+        H += (uint32_t)__popcll(__ballot(hit) & gmask);
+      }
+    } else {
     uint4 next = w.umeta[min(u0 + l, u1 - 1)], next2 = w.umeta[min(u0 + G + l, u1 - 1)];
     int32_t cnext = !lru ? dv.cnt[next.x] : 0;
     for (uint32_t c = u0; c < u1; c += G) {
@@ -810,6 +855,7 @@ __device__ __forceinline__ void decide_sets(const Dev& dv, const Work& w, TabPre
       M += (uint32_t)__popcll(mm);
       H += (uint32_t)__popcll(__ballot(hit) & gmask);
     }
+    }
     __builtin_amdgcn_wave_barrier();
     if (l == 0) ps.hits += H;
     if (M == 0) continue;
@@ -818,6 +864,7 @@ __device__ __forceinline__ void decide_sets(const Dev& dv, const Work& w, TabPre
     if (l < A) {
       const int32_t hu = L.hitu[lane];
       if (tg < 0) vpv = LLONG_MIN;
+      else if (PROBED) {}  // as loaded
       else if (lru) vpv = hu >= 0 ? (long long)(int32_t)step : vpv;
       else vpv = hu >= 0 ? (long long)hitc[lane] : (long long)dv.cnt[td.row_base + tg];
     }
@@ -1066,7 +1113,7 @@ __device__ __forceinline__ void sum_jobs(const Dev& dv, const Work& w, TabPrefix
 
 // Workgroups below n_sum take the gradient sums (the longer chains, started first), the
 // others the sets.
-template <int D, int G>
+template <int D, int G, bool PROBED>
 __global__ __launch_bounds__(256) void k_decide(Dev dv, Work w, const uint32_t* __restrict__ sval,
                                                 const float* __restrict__ grad, uint32_t step, int nblk, int nb_shift,
                                                 int cshift, int n_sum) {
@@ -1086,7 +1133,7 @@ __global__ __launch_bounds__(256) void k_decide(Dev dv, Work w, const uint32_t* 
     sum_jobs<D>(dv, w, P, grad, sval, nblk, nb_shift, cshift, (int)blockIdx.x, n_sum);
   } else {
     if (!tab_prefix(P, w.tab_info, dv.T, [](const TabInfo& x) { return x.sets; })) return;
-    decide_sets<G>(dv, w, P, step, (int)blockIdx.x - n_sum, (int)gridDim.x - n_sum);
+    decide_sets<G, PROBED>(dv, w, P, step, (int)blockIdx.x - n_sum, (int)gridDim.x - n_sum);
   }
 }
 
@@ -1292,14 +1339,18 @@ hipError_t launch_backward_small(const Dev& d, const Work& w, const int32_t* idx
     const uint32_t* sk = nullptr;
     const hipError_t e = launch_mid_front(d, w, idx, L, off, B, passes, G, &sk, &sval, s);
     if (e != hipSuccess) return e;
-    const unsigned rounds = (unsigned)std::min<int64_t>((L + kMidRows - 1) / kMidRows, 1024);
-    k_mid_rows<<<rounds, 256, 0, s>>>(d, w, sk, sval);
+    if (decay && d.cnt) k_decay_small<<<grid_for(d.total_rows), 256, 0, s>>>(d.cnt, d.total_rows, w.tab_info, d.T);
+    const auto rows = [&](auto kernel, int per) {
+      kernel<<<(unsigned)std::min<int64_t>((L + 256 * per - 1) / (256 * per), 1024), 256, 0, s>>>(d, w, sk, sval, step);
+    };
+    if (L < (1 << 19)) d.assoc <= 16 ? rows(k_mid_rows<16, 1>, 1) : rows(k_mid_rows<64, 1>, 1);
+    else d.assoc <= 16 ? rows(k_mid_rows<16, 4>, 4) : rows(k_mid_rows<64, 4>, 4);
   } else {
     k_front<<<(unsigned)d.T, kFrontThreads, 0, s>>>(d, w, idx, L, off, B, passes, G);
+    if (decay && d.cnt) k_decay_small<<<grid_for(d.total_rows), 256, 0, s>>>(d.cnt, d.total_rows, w.tab_info, d.T);
   }
   const uint32_t direct = mid ? kMidDirect : kSmallDirect;
   const int cshift = mid ? kMidChunkShift : kSmallChunkShift;
-  if (decay && d.cnt) k_decay_small<<<grid_for(d.total_rows), 256, 0, s>>>(d.cnt, d.total_rows, w.tab_info, d.T);
   return dispatch_row(d.dim, d.bits, d.sb16, [&]<int D, int BITS, bool SB16>() -> hipError_t {
     // a set or a row per lookup, a chunk per direct + 1 at most
     const auto blocks = [](int64_t items, int per, int64_t cap) {
@@ -1310,9 +1361,9 @@ hipError_t launch_backward_small(const Dev& d, const Work& w, const int32_t* idx
     const auto decide = [&](auto kernel) {
       kernel<<<(unsigned)(n_sum + n_set), 256, 0, s>>>(d, w, sval, grad, step, nblk, nb_shift, cshift, n_sum);
     };
-    if (G == 16) decide(k_decide<D, 16>);
-    else if (G == 32) decide(k_decide<D, 32>);
-    else decide(k_decide<D, 64>);
+    if (G == 16) mid ? decide(k_decide<D, 16, true>) : decide(k_decide<D, 16, false>);
+    else if (G == 32) mid ? decide(k_decide<D, 32, true>) : decide(k_decide<D, 32, false>);
+    else mid ? decide(k_decide<D, 64, true>) : decide(k_decide<D, 64, false>);
     if (nblk > kFoldInline && L > (int64_t)kBlockAbove)
       k_fold<D><<<(unsigned)blocks(L / kBlockAbove, 1, 1024), 256, 0, s>>>(d, w, nblk);
     if (update_events) {
