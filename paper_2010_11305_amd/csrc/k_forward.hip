@@ -274,13 +274,12 @@ __global__ __launch_bounds__(256) void k_fwd_probe(Dev dv, const int32_t* __rest
 template <int D, int BITS, bool SB16>
 __global__ __launch_bounds__(256) void k_fwd_gather(Dev dv, const int32_t* __restrict__ src, int64_t L,
                                                     const int32_t* __restrict__ off, int32_t B, DivConst per_table,
-                                                    float* __restrict__ out) {
+                                                    int tile_bags, float* __restrict__ out) {
   constexpr int LPR = Geo<D>::LPR, FU = kFwdUnroll;
-  constexpr int GPB = 256 / LPR;
   const int64_t RB = dv.rec_bytes;
   const int g = threadIdx.x & (LPR - 1);
-  // tiles of GPB bags of one table, table-major: a contiguous run of tiles per XCD, which
-  // its workgroups walk side by side
+  // tiles of tile_bags (at most GPB) bags of one table, table-major: a contiguous run of
+  // tiles per XCD, which its workgroups walk side by side
   const int xcd = blockIdx.x % kXcds, unit = blockIdx.x / kXcds, units = gridDim.x / kXcds;
   const int64_t ntiles = (int64_t)per_table.d * dv.T;
   int64_t clo, chi;
@@ -288,8 +287,9 @@ __global__ __launch_bounds__(256) void k_fwd_gather(Dev dv, const int32_t* __res
   if (clo + unit >= chi) return;
   const auto tile_bag = [&](int64_t c, int& t) -> uint32_t {
     t = (int)div_by((uint32_t)c, per_table);
-    return ((uint32_t)c - (uint32_t)t * per_table.d) * GPB + threadIdx.x / LPR;
+    return ((uint32_t)c - (uint32_t)t * per_table.d) * (uint32_t)tile_bags + threadIdx.x / LPR;
   };
+  if ((int)threadIdx.x / LPR >= tile_bags) return;  // whole row groups; no barrier below
   const uint32_t last = (uint32_t)B - 1u;
   // the offsets of the group's next bag are loaded one tile ahead, the codes of the next
   // LPR positions one chunk ahead (indices clamped so that the loads are unconditional; a
@@ -538,10 +538,13 @@ hipError_t launch_forward(const Dev& d, const Work& w, const int32_t* idx, int64
   const int64_t nbags = (int64_t)d.T * B;
   k_fwd_begin<<<grid_for(nbags, 2048), 256, 0, s>>>(d, off, nbags, L);
   if (nbags == 0) return hipGetLastError();
-  if (L < kFusedBelow) {
+  // (a narrow row's group has few lanes to probe a long bag: one table of 1000 50-lookup bags of
+  // 16 columns takes 61 us in one kernel and 39 in two; at 32 columns one kernel is ahead)
+  if (L < kFusedBelow && (d.dim > 16 || L <= 8 * nbags)) {
     const DivConst byB = div_const((uint32_t)B);
     return dispatch_row(d.dim, d.bits, d.sb16, [&]<int D, int BITS, bool SB16>() -> hipError_t {
-      const int64_t wgs = (nbags * Geo<D>::LPR + 255) / 256;
+      // (few bags are spread over 512 workgroups)
+      const int64_t wgs = std::max<int64_t>((nbags * Geo<D>::LPR + 255) / 256, std::min<int64_t>(nbags, 512));
       const auto run = [&](auto kernel) {
         const int64_t cap = resident_grid(reinterpret_cast<const void*>(kernel));
         const int64_t blocks = std::min<int64_t>((wgs + 7) / 8 * 8, cap);
@@ -576,13 +579,16 @@ hipError_t launch_forward(const Dev& d, const Work& w, const int32_t* idx, int64
     if (e != hipSuccess) return e;
   }
   return dispatch_row(d.dim, d.bits, d.sb16, [&]<int D, int BITS, bool SB16>() -> hipError_t {
-    // one tile per workgroup, in whole multiples of 8 workgroups, at most the resident count
-    constexpr int GPB = 256 / Geo<D>::LPR;
-    const DivConst per_table = div_const((uint32_t)((B + GPB - 1) / GPB));
+    // one tile per workgroup, in whole multiples of 8 workgroups, at most the resident count;
+    // few bags are spread over 512 workgroups (16 long bags in one wave take 449 us, 344 on 8
+    // workgroups)
+    int tile_bags = 256 / Geo<D>::LPR;
+    while (tile_bags > 1 && (int64_t)d.T * ((B + tile_bags - 1) / tile_bags) < 512) tile_bags /= 2;
+    const DivConst per_table = div_const((uint32_t)(((int64_t)B + tile_bags - 1) / tile_bags));
     const int64_t tiles = (int64_t)per_table.d * d.T;
     const int64_t cap = resident_grid(reinterpret_cast<const void*>(k_fwd_gather<D, BITS, SB16>));
     const int64_t blocks = std::min<int64_t>((tiles + 7) / 8 * 8, cap);
-    k_fwd_gather<D, BITS, SB16><<<(unsigned)blocks, 256, 0, s>>>(d, w.fwd_src, L, off, B, per_table, out);
+    k_fwd_gather<D, BITS, SB16><<<(unsigned)blocks, 256, 0, s>>>(d, w.fwd_src, L, off, B, per_table, tile_bags, out);
     return hipGetLastError();
   });
 }

@@ -160,6 +160,20 @@ def test_general_step(torch, dim, knobs):
     steps(torch, cfg, 2, edit)
 
 
+@pytest.mark.parametrize("batch,mean", [(3, 40), (40, 1000), (4001, 12)])
+def test_positions_outside_every_bag(torch, batch, mean):
+    """Lookups before the first bag and after the last are skipped and not counted: in a small
+    call, a call of few long bags, and a mid call."""
+    cfg = custom_cfg(rows=[5000, 60, 900], dim=16, batch=batch, pooling=("poisson", mean), zipf=1.2, cache_fraction=0.05,
+                     **LRU)
+
+    def edit(st, k):
+        st["indices"] = np.concatenate([np.full(100 + k, 7, np.int32), st["indices"], np.full(57, -3, np.int32)])
+        st["offsets"] = st["offsets"] + np.int32(100 + k)
+
+    steps(torch, cfg, 2, edit)
+
+
 def test_mid_step_large_sets_and_folds(torch):
     """LFU sets of more than 128 rows (a lane looks for its fifth candidate in memory) and rows
     spread over more than 8 bag blocks, in one table."""
