@@ -8,6 +8,7 @@
 #include "emb_cache.h"
 #include "embc_device.h"
 #include "embc_dispatch.h"
+#include "embc_offsets.h"
 #include "embc_sort.h"
 
 namespace embc {
@@ -386,8 +387,7 @@ __global__ __launch_bounds__(256) void k_fwd_begin(Dev dv, const int32_t* __rest
   zero_stats(dv, kStInvalidFwd, kStInvalidFwd);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nbags; i += stride) {
-    const int64_t a = off[i], b = off[i + 1];
-    if (a < 0 || b < a || b > L) atomicOr(dv.err, kErrOffsets);
+    if (bad_range(off[i], off[i + 1], L)) atomicOr(dv.err, kErrOffsets);
   }
 }
 

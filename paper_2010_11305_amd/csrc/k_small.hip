@@ -18,6 +18,7 @@
 
 #include "embc_device.h"
 #include "embc_dispatch.h"
+#include "embc_offsets.h"
 #include "embc_row.h"
 
 namespace embc {
@@ -195,7 +196,7 @@ __device__ __forceinline__ bool front_expand(FrontLds& S, const FrontTab& f, con
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int b = bt + q * kFrontThreads;
-      bad |= x[q] < 0 || y[q] < x[q] || (int64_t)y[q] > f.L;
+      bad |= bad_range(x[q], y[q], f.L);
       // (out of range where the offsets are bad, or in another tile)
       const int64_t at = (int64_t)x[q] - f.P0 - t0;
       if (b < b1 && y[q] > x[q] && at >= 0 && at < m) S.val[at] = (uint32_t)b + 1u;
@@ -382,7 +383,7 @@ __device__ __forceinline__ bool front_large(FrontLds& S, const Work& w, const Fr
     for (int q = 0; q < 8; ++q) {
       const int b = min(b0 + q * kFrontThreads, f.B - 1);
       const int32_t a = f.offt[b], e = f.offt[b + 1];
-      x[q] = a < 0 || e < a || (int64_t)e > f.L;
+      x[q] = bad_range(a, e, f.L);
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q) bad |= x[q] != 0;
@@ -430,7 +431,7 @@ __device__ __forceinline__ bool front_large(FrontLds& S, const Work& w, const Fr
 }
 
 // Workgroup t handles table t alone and changes no state but the table's statistics (a bad
-// offset of another table rejects the call: the kernels after this one look at every
+// offset inside another table rejects the call: the kernels after this one look at every
 // table's flag).  Its time at 2048 lookups is about a chain of 12 barriers and memory
 // round trips per digit pass and list, not bandwidth: one workgroup holds the keys in
 // LDS and registers from the expansion to the lists.
@@ -450,7 +451,9 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(Dev dv, Work w, const i
   }
   const int32_t* offt = off + (int64_t)t * B;
   const int64_t p0 = B > 0 ? offt[0] : 0, p1 = B > 0 ? offt[B] : 0;
-  bool bad = p0 < 0 || p1 < p0 || p1 > L;  // whole workgroup, as below
+  // every workgroup looks at all tables' boundaries before it writes: its positions are then its
+  // own (its bags inside them are checked as they are expanded)
+  bool bad = __syncthreads_or(B > 0 && bad_boundaries(off, dv.T, B, L, tid, kFrontThreads)) != 0;
   const uint32_t P0 = bad ? 0u : (uint32_t)p0, n = bad ? 0u : (uint32_t)(p1 - p0);
   const FrontTab f{idx + P0, offt, B, L, P0, n};
   if (tid == 0) S.n_bad = S.n_chunk = S.n_big = 0;

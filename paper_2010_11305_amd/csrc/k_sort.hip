@@ -10,6 +10,7 @@
 
 #include "embc_device.h"
 #include "embc_dispatch.h"
+#include "embc_offsets.h"
 #include "embc_sort.h"
 
 namespace embc {
@@ -725,8 +726,7 @@ __global__ __launch_bounds__(256) void k_mid_begin(Dev dv, Work w, const int32_t
   for (int64_t i = tid; i < (int64_t)T * kMaxPasses * 256; i += stride) sg.hist[i] = 0;
   bool bad = false;
   for (int64_t i = tid; i < (int64_t)T * B; i += stride) {
-    const int64_t a = off[i], b = off[i + 1];
-    bad |= a < 0 || b < a || b > L;
+    bad |= bad_range(off[i], off[i + 1], L);
   }
   bad = __syncthreads_or(bad) != 0;
   if (threadIdx.x == 0) {
@@ -1158,8 +1158,7 @@ __global__ __launch_bounds__(256) void k_check_offsets(Dev dv, const int32_t* __
                                                        int64_t L, unsigned long long* __restrict__ ctr) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nbags; i += stride) {
-    const int64_t a = off[i], b = off[i + 1];
-    if (a < 0 || b < a || b > L) {
+    if (bad_range(off[i], off[i + 1], L)) {
       ctr[kCBadOffsets] = 1;
       atomicOr(dv.err, kErrOffsets);
     }

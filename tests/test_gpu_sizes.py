@@ -204,3 +204,30 @@ def test_malformed_offsets_reject_the_call(torch, batch):
         compare_state(o, g, cfg)
     step_both(o, g, cfg, workload.make_step(cfg, 2), torch)
     compare_state(o, g, cfg)
+
+
+@pytest.mark.parametrize("n", [3000, 20_000])
+def test_tables_that_share_positions_reject_the_call(torch, n):
+    """A small call of three tables of which the first and the last cover the same n lookups (each
+    valid by itself; the one between runs backwards): no table changes, the statistics read 0
+    (in LDS, and in memory by tiles)."""
+    from paper_2010_11305_amd import emb_cache as ec
+    B = 2
+    cfg = custom_cfg(rows=[40_000, 300, 50_000], batch=B, **LRU)
+    o, g = make_pair(cfg, max_indices=n)
+    rng = np.random.default_rng(n)
+    idx = rng.integers(0, 40_000, n).astype(np.int32)
+    off = np.array([0, n // 2, n, n, 0, n // 3, n], dtype=np.int32)
+    grad = rng.standard_normal((B, 3, cfg["dim"])).astype(np.float32)
+    log(f"tables that share {n} positions")
+    g.backward_update(torch.from_numpy(idx).cuda(), torch.from_numpy(off).cuda(), B, torch.from_numpy(grad).cuda())
+    o.backward_update(idx, off, B, grad)
+    torch.cuda.synchronize()
+    assert g.check() == ec.EMB_EINDEX
+    for t in range(3):
+        s = g.stats(t)
+        assert all(s[f] == 0 for f in ec.STAT_NAMES[2:10]) and s["invalid_bwd"] == 0
+    compare_state(o, g, cfg)
+    off = np.array([0, n // 3, n // 2, n // 2, n // 2, n - 5, n], dtype=np.int32)
+    step_both(o, g, cfg, {"indices": idx, "offsets": off, "batch": B, "grad": grad}, torch)
+    compare_state(o, g, cfg)
