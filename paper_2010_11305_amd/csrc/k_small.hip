@@ -820,7 +820,8 @@ __device__ __forceinline__ void decide_sets(const Dev& dv, const Work& w, TabPre
       if (A >= 4) {
         for (int j = 0; j < A; j += 4) {
           const int4 tj = *reinterpret_cast<const int4*>(tags + gb + j);
-          way = tj.x == r ? j : tj.y == r ? j + 1 : tj.z == r ? j + 2 : tj.w == r ? j + 3 : way;
+          // (the last way that holds the row, as probe_set: an imported cache may hold it twice)
+          way = tj.w == r ? j + 3 : tj.z == r ? j + 2 : tj.y == r ? j + 1 : tj.x == r ? j : way;
         }
       } else {
         for (int j = 0; j < A; ++j) way = tags[gb + j] == r ? j : way;

@@ -231,3 +231,33 @@ def test_tables_that_share_positions_reject_the_call(torch, n):
     off = np.array([0, n // 3, n // 2, n // 2, n // 2, n - 5, n], dtype=np.int32)
     step_both(o, g, cfg, {"indices": idx, "offsets": off, "batch": B, "grad": grad}, torch)
     compare_state(o, g, cfg)
+
+
+@pytest.mark.parametrize("batch", [8, 30_000])
+@pytest.mark.parametrize("assoc,ways", [(2, (0, 1)), (4, (1, 2)), (8, (3, 6)), (16, (4, 5))])
+def test_row_that_an_imported_cache_holds_twice(torch, batch, assoc, ways):
+    """emb_cache_import_cache takes a set that holds a row in two ways; the last one is the row's,
+    for the forward and for the step, in a small and in a mid call: the step changes that way
+    alone (the other keeps its values and its stamp)."""
+    cfg = custom_cfg(rows=[64], batch=batch, cache_fraction=assoc / 64, assoc=assoc, policy="lru", lr=1.0)
+    _, g = make_pair(cfg, max_indices=batch)
+    assert g.n_sets == [1]
+    d = cfg["dim"]
+    tag = np.full(assoc, -1, np.int32)
+    tag[list(ways)] = 7
+    crow = np.zeros((assoc, d), np.float32)
+    crow[ways[0]], crow[ways[1]] = 3.0, 5.0
+    ts = np.where(tag >= 0, 2, -1).astype(np.int32)
+    g.import_cache(0, crow, tag, ts)
+    g.step = 9
+    idx = torch.full((batch,), 7, dtype=torch.int32, device="cuda")
+    off = torch.arange(batch + 1, dtype=torch.int32, device="cuda")
+    log(f"row held twice, {assoc} ways, {batch} lookups")
+    assert torch.all(g.forward(idx, off, batch) == 5.0)
+    grad = torch.zeros((batch, 1, d), device="cuda")
+    grad[0] = 1.0
+    g.backward_update(idx, off, batch, grad)
+    c = g.export_cache(0)
+    assert np.all(c["crow"][ways[0]] == 3.0) and np.all(c["crow"][ways[1]] == 4.0)
+    assert c["ts"][ways[0]] == 2 and c["ts"][ways[1]] == 9
+    assert g.stats(0)["unique_hits"] == 1 and g.check() == 0
