@@ -137,13 +137,15 @@ constexpr bool small_call(int64_t L, int32_t B, int T) {
 }
 
 // The lists of one table in a small or mid call, at offsets that follow from pos: unique rows
-// and sets from pos on, chunk sums from pos/8 (pos/16 in a mid call), big rows from pos/512.
+// and sets from pos on, chunk sums from pos/8 (pos/16 in a mid call), big rows from pos/512, their
+// windows from pos/32.
 struct TabInfo {
   uint32_t pos;     // its first lookup
   uint32_t rows;    // unique rows
   uint32_t sets;    // touched sets (without a cache: runs of rows)
   uint32_t chunks;  // chunk sums
   uint32_t big;     // rows with more than kBlockAbove lookups
+  uint32_t windows; // windows of those rows' lookups
   uint32_t bad;     // its offsets were rejected
   uint32_t skipped; // lookups out of range (mid calls)
   uint32_t valid;   // the others (mid calls)
@@ -165,6 +167,15 @@ constexpr bool mid_call(int64_t L, int32_t B, int T) {
 // has at least one more; the chunk sums of a table start at pos >> shift.
 constexpr uint32_t kSmallDirect = 8, kMidDirect = 16;
 constexpr int kSmallChunkShift = 3, kMidChunkShift = 4;
+// The block sums of a row with more than kBlockAbove lookups are taken in windows: one bag block
+// each if the call's blocks hold kWindow of its lookups on average, else kWindow of its
+// lookups each (so c lookups have at most c >> kWindowShift windows).
+constexpr uint32_t kWindow = 64;
+constexpr int kWindowShift = 5;
+constexpr bool block_windows(uint32_t c, int nblk) { return c >= (uint64_t)kWindow * (uint32_t)nblk; }
+constexpr uint32_t windows_of(uint32_t c, int nblk) {
+  return block_windows(c, nblk) ? (uint32_t)nblk : (c + kWindow - 1) / kWindow;
+}
 
 // Per-call temporaries carved from the caller's workspace buffer.
 struct Work {
@@ -203,7 +214,8 @@ struct Work {
   int32_t* tab_first;    // [T+1] first unique row of each table (tab_first[T] = number of unique rows)
   int32_t* fwd_src;      // [L] forward: cache slot of each lookup, -2-row for a miss, -1 if skipped
   unsigned long long* ctr;  // counters, see kC*
-  TabInfo* tab_info;     // [T] small calls
+  TabInfo* tab_info;     // [T] small and mid calls
+  uint4* big_window;     // [L/32 + 1] small and mid calls: big row, its window, the row's lookups [z, w)
   int64_t max_indices;
   int64_t max_partials;
 };

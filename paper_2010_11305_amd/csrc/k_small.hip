@@ -77,7 +77,7 @@ struct FrontLds {
   uint32_t hist[kMaxPasses][256];  // a table in memory: digit counts of every pass, then the digits' ends
   unsigned long long scan[kFrontWaves];
   uint32_t rows[kFrontItems * kFrontWaves], sets[kFrontItems * kFrontWaves];  // starts per run of 64 keys
-  uint32_t n_bad, n_chunk, n_big;
+  uint32_t n_bad, n_chunk, n_big, n_window;
 };
 
 // Ranks of ITEMS keys per thread (wave-major order: item i of wave w is key w*64*ITEMS +
@@ -152,6 +152,20 @@ __device__ __forceinline__ void front_sort(FrontLds& S, uint32_t (&k)[ITEMS], ui
       }
     }
     __syncthreads();
+  }
+}
+
+// The windows of the lanes' big rows (big: the lane has one, row h, whose lookups are [s0, s1) of
+// the sorted stream; its windows go from entry `at` on), by the whole wave: one lane alone
+// would write the hundreds of a hot row one after another.
+__device__ __forceinline__ void put_windows(const Work& w, bool big, uint32_t at, uint32_t h, uint32_t s0, uint32_t s1,
+                                            int nblk) {
+  for (uint64_t m = __ballot(big); m; m &= m - 1) {
+    const int src = (int)__builtin_ctzll(m);
+    const uint32_t a = __builtin_amdgcn_readlane(at, src), row = __builtin_amdgcn_readlane(h, src);
+    const uint32_t b0 = __builtin_amdgcn_readlane(s0, src), b1 = __builtin_amdgcn_readlane(s1, src);
+    const uint32_t n = windows_of(b1 - b0, nblk);
+    for (uint32_t j = threadIdx.x & 63; j < n; j += 64) w.big_window[a + j] = make_uint4(row, j, b0, b1);
   }
 }
 
@@ -437,7 +451,7 @@ __device__ __forceinline__ bool front_large(FrontLds& S, const Work& w, const Fr
 // LDS and registers from the expansion to the lists.
 __global__ __launch_bounds__(kFrontThreads) void k_front(Dev dv, Work w, const int32_t* __restrict__ idx, int64_t L,
                                                          const int32_t* __restrict__ off, int32_t B, int passes,
-                                                         int group) {
+                                                         int group, int nblk) {
   __shared__ FrontLds S;
   const int t = blockIdx.x, tid = threadIdx.x;
   const TableDesc td = dv.desc[t];
@@ -456,7 +470,7 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(Dev dv, Work w, const i
   bool bad = __syncthreads_or(B > 0 && bad_boundaries(off, dv.T, B, L, tid, kFrontThreads)) != 0;
   const uint32_t P0 = bad ? 0u : (uint32_t)p0, n = bad ? 0u : (uint32_t)(p1 - p0);
   const FrontTab f{idx + P0, offt, B, L, P0, n};
-  if (tid == 0) S.n_bad = S.n_chunk = S.n_big = 0;
+  if (tid == 0) S.n_bad = S.n_chunk = S.n_big = S.n_window = 0;
   // expanded, sorted by the local key (a skipped lookup's digits are all 255, above every
   // valid key's, so skipped lookups end the table's run), unique rows and sets listed
   const bool in_lds = n <= (uint32_t)kFrontTile;
@@ -471,7 +485,7 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(Dev dv, Work w, const i
   }
   if (bad) {
     if (tid == 0) {
-      w.tab_info[t] = TabInfo{0, 0, 0, 0, 0, 1, 0, 0};
+      w.tab_info[t] = TabInfo{.bad = 1};
       atomicOr(dv.err, kErrOffsets);
     }
     return;
@@ -484,33 +498,35 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(Dev dv, Work w, const i
 
   // ---- per unique row: the update's inputs, and the jobs of the gradient sums (their order
   // inside a table does not matter).  A row of more than kSmallDirect lookups has at most one
-  // chunk per 9 of them and a row of more than kBlockAbove is one per 513, so the jobs of a
-  // table fit the 1/8 and 1/512 of its positions.
+  // chunk per 9 of them and a row of more than kBlockAbove is one per 513, with a window per
+  // 32, so the jobs of a table fit the 1/8, 1/512 and 1/32 of its positions.
   const uint32_t cbase = P0 >> kSmallChunkShift, hbase = P0 >> 9;
-  for (uint32_t i0 = tid; i0 < nU; i0 += 4 * kFrontThreads) {
+  for (uint32_t base = 0; base < nU; base += 4 * kFrontThreads) {  // whole waves
     uint32_t s0[4], s1[4], bag[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const uint32_t i = min(i0 + q * kFrontThreads, nU - 1);
+      const uint32_t i = min(base + q * kFrontThreads + tid, nU - 1);
       s0[q] = first[i];
       s1[q] = i + 1 < nU ? first[i + 1] : nv;
       bag[q] = vb[s0[q]];  // used by a row with one lookup
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const uint32_t u = P0 + i0 + q * kFrontThreads;
-      if (i0 + q * kFrontThreads >= nU) break;
+      if (base + q * kFrontThreads >= nU) break;
+      const bool live = base + q * kFrontThreads + tid < nU;
+      const uint32_t u = P0 + base + q * kFrontThreads + tid;
       const uint32_t c = s1[q] - s0[q], key = sk[s0[q]];
       uint32_t r = key;
       if (td.n_sets > 0) {
         const uint32_t set = div_by(key, td.by_Q);
         r = (key - set * (uint32_t)td.Q) * (uint32_t)td.n_sets + set;
       }
-      uint32_t aux = 0;
-      if (c > kBlockAbove) {
+      const bool big = live && c > kBlockAbove;
+      uint32_t aux = 0, window = 0;
+      if (big) {
         aux = hbase + atomicAdd(&S.n_big, 1u);
-        w.big_rows[aux] = (int32_t)u;
-      } else if (c > kSmallDirect) {
+        window = (P0 >> kWindowShift) + atomicAdd(&S.n_window, windows_of(c, nblk));
+      } else if (live && c > kSmallDirect) {
         const uint32_t nc = (c + kSumChunk - 1) / kSumChunk;
         aux = cbase + atomicAdd(&S.n_chunk, nc);
         for (uint32_t j = 0; j < nc; ++j) {
@@ -518,12 +534,13 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(Dev dv, Work w, const i
           w.chunk_span[aux + j] = make_uint2(a, min(a + (uint32_t)kSumChunk, P0 + s1[q]));
         }
       }
-      w.umeta[u] = make_uint4((uint32_t)td.row_base + r, aux, c == 1 ? bag[q] : P0 + s0[q], c);
+      if (live) w.umeta[u] = make_uint4((uint32_t)td.row_base + r, aux, c == 1 ? bag[q] : P0 + s0[q], c);
+      put_windows(w, big, window, aux, P0 + s0[q], P0 + s1[q], nblk);
     }
   }
   __syncthreads();
   if (tid == 0) {
-    w.tab_info[t] = TabInfo{P0, nU, nS, S.n_chunk, S.n_big, 0, n - nv, nv};
+    w.tab_info[t] = TabInfo{P0, nU, nS, S.n_chunk, S.n_big, S.n_window, 0, n - nv, nv};
     unsigned long long* st = dv.stats + ((int64_t)t << dv.stat_shift) * kStatStride;
     st[kStBwdLookups] = nv;
     st[kStInvalidBwd] = n - nv;
@@ -595,10 +612,10 @@ __device__ __forceinline__ int tab_of(const TabPrefix& P, int T, uint32_t i) {
 // per row).
 template <int MAXA, int PER>
 __global__ __launch_bounds__(256) void k_mid_rows(Dev dv, Work w, const uint32_t* __restrict__ sk,
-                                                  const uint32_t* __restrict__ sval, uint32_t step) {
+                                                  const uint32_t* __restrict__ sval, uint32_t step, int nblk) {
   __shared__ TabPrefix P;
   __shared__ unsigned long long part[4];
-  __shared__ uint32_t at_s[2];
+  __shared__ uint32_t at_s[3];
   if (!tab_prefix(P, w.tab_info, dv.T, [](const TabInfo& x) { return x.rows; })) return;
   constexpr uint32_t kRows = 256 * PER;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -608,7 +625,7 @@ __global__ __launch_bounds__(256) void k_mid_rows(Dev dv, Work w, const uint32_t
     const int ta = tab_of(P, dv.T, r0), tb = tab_of(P, dv.T, rend - 1);  // whole workgroup
     uint32_t s0[PER], c[PER], key[PER], bag[PER];
     int tt[PER];
-    unsigned long long jobs = 0;  // chunks | big rows << 32
+    unsigned long long jobs = 0;  // chunks | big rows << 20 | windows << 40 (at most 512 per row)
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
       const uint32_t i = min(r0 + (uint32_t)(q * 256) + threadIdx.x, rend - 1);
@@ -623,7 +640,8 @@ __global__ __launch_bounds__(256) void k_mid_rows(Dev dv, Work w, const uint32_t
       key[q] = sk[s0[q]];
       bag[q] = sval[s0[q]];
       if (r0 + (uint32_t)(q * 256) + threadIdx.x >= rend) c[q] = 0;
-      jobs += c[q] > kBlockAbove ? (1ull << 32) : c[q] > kMidDirect ? (c[q] + kSumChunk - 1) / kSumChunk : 0u;
+      jobs += c[q] > kBlockAbove ? (1ull << 20) + ((unsigned long long)windows_of(c[q], nblk) << 40)
+                                 : c[q] > kMidDirect ? (c[q] + kSumChunk - 1) / kSumChunk : 0u;
     }
     unsigned long long x = jobs;
 #pragma unroll
@@ -639,29 +657,27 @@ __global__ __launch_bounds__(256) void k_mid_rows(Dev dv, Work w, const uint32_t
       if (k < wv) pre += part[k];
       tot += part[k];
     }
-    if (ta == tb && threadIdx.x < 2) {
-      const uint32_t n = threadIdx.x == 0 ? (uint32_t)tot : (uint32_t)(tot >> 32);
-      uint32_t* count = threadIdx.x == 0 ? &w.tab_info[ta].chunks : &w.tab_info[ta].big;
-      at_s[threadIdx.x] = n ? atomicAdd(count, n) : 0u;
+    if (ta == tb && threadIdx.x < 3) {
+      const uint32_t n = (uint32_t)(tot >> (20 * threadIdx.x)) & (threadIdx.x < 2 ? 0xFFFFFu : ~0u);
+      TabInfo& ti = w.tab_info[ta];
+      at_s[threadIdx.x] = n ? atomicAdd(threadIdx.x == 0 ? &ti.chunks : threadIdx.x == 1 ? &ti.big : &ti.windows, n) : 0u;
     }
     __syncthreads();
-    uint32_t chunk_at = ta == tb ? at_s[0] + (uint32_t)pre : 0u, big_at = ta == tb ? at_s[1] + (uint32_t)(pre >> 32) : 0u;
+    // (where this thread's jobs go; a workgroup across a table boundary places them one by one)
+    uint32_t chunk_at = at_s[0] + ((uint32_t)pre & 0xFFFFFu), big_at = at_s[1] + ((uint32_t)(pre >> 20) & 0xFFFFFu),
+             window_at = at_s[2] + (uint32_t)(pre >> 40);
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-      if (c[q] == 0) continue;
+      const bool live = c[q] != 0, big = c[q] > kBlockAbove;
       const int t = tt[q];
       const uint32_t pos = w.tab_info[t].pos;
-      const uint32_t u = pos + r0 + (uint32_t)(q * 256) + threadIdx.x - P.pre[t];
       const TableDesc& td = dv.desc[t];
-      uint32_t r = key[q] - (uint32_t)td.key_base;
-      if (td.n_sets > 0) {
-        const uint32_t set = div_by(r, td.by_Q);
-        r = (r - set * (uint32_t)td.Q) * (uint32_t)td.n_sets + set;
-      }
-      uint32_t aux = 0;
-      if (c[q] > kBlockAbove) {
+      uint32_t aux = 0, window = 0;
+      if (big) {
+        const uint32_t nw = windows_of(c[q], nblk);
         aux = (pos >> 9) + (ta == tb ? big_at++ : atomicAdd(&w.tab_info[t].big, 1u));
-        w.big_rows[aux] = (int32_t)u;
+        window = (pos >> kWindowShift) + (ta == tb ? window_at : atomicAdd(&w.tab_info[t].windows, nw));
+        window_at += nw;
       } else if (c[q] > kMidDirect) {
         const uint32_t nc = (c[q] + kSumChunk - 1) / kSumChunk;
         if (ta == tb) {
@@ -675,19 +691,28 @@ __global__ __launch_bounds__(256) void k_mid_rows(Dev dv, Work w, const uint32_t
           w.chunk_span[aux + j] = make_uint2(a, min(a + (uint32_t)kSumChunk, s0[q] + c[q]));
         }
       }
-      const uint32_t grow = (uint32_t)td.row_base + r;
-      w.umeta[u] = make_uint4(grow, aux, c[q] == 1 ? bag[q] : s0[q], c[q]);
-      const int32_t slot = probe_slot<MAXA>(dv, td, (int32_t)r);
-      w.uslot[u] = slot;
-      w.uact[u] = slot >= 0 ? kActHitStay : kActBypass;
-      if (dv.policy == 0) {
-        if (slot >= 0) dv.ts[slot] = (int32_t)step;
-      } else {
-        const int64_t cc = (int64_t)dv.cnt[grow] + c[q];
-        const int32_t cn = cc > 0x7FFFFFFF ? 0x7FFFFFFF : (int32_t)cc;
-        dv.cnt[grow] = cn;
-        w.ukey[u] = slot >= 0 ? 0ull : ((unsigned long long)(uint32_t)cn << 32) | (uint32_t)~grow;
+      if (live) {
+        const uint32_t u = pos + r0 + (uint32_t)(q * 256) + threadIdx.x - P.pre[t];
+        uint32_t r = key[q] - (uint32_t)td.key_base;
+        if (td.n_sets > 0) {
+          const uint32_t set = div_by(r, td.by_Q);
+          r = (r - set * (uint32_t)td.Q) * (uint32_t)td.n_sets + set;
+        }
+        const uint32_t grow = (uint32_t)td.row_base + r;
+        w.umeta[u] = make_uint4(grow, aux, c[q] == 1 ? bag[q] : s0[q], c[q]);
+        const int32_t slot = probe_slot<MAXA>(dv, td, (int32_t)r);
+        w.uslot[u] = slot;
+        w.uact[u] = slot >= 0 ? kActHitStay : kActBypass;
+        if (dv.policy == 0) {
+          if (slot >= 0) dv.ts[slot] = (int32_t)step;
+        } else {
+          const int64_t cc = (int64_t)dv.cnt[grow] + c[q];
+          const int32_t cn = cc > 0x7FFFFFFF ? 0x7FFFFFFF : (int32_t)cc;
+          dv.cnt[grow] = cn;
+          w.ukey[u] = slot >= 0 ? 0ull : ((unsigned long long)(uint32_t)cn << 32) | (uint32_t)~grow;
+        }
       }
+      put_windows(w, big, window, aux, s0[q], s0[q] + c[q], nblk);
     }
   }
 }
@@ -1004,20 +1029,22 @@ __device__ __forceinline__ void sum_span(const uint32_t* __restrict__ sval, uint
 
 // The same sum of a long span by a whole wave, for rows of up to 64 columns: 8 loads of 64
 // lanes, 16 bytes each, bring 2048/d rows at once (16 lanes of 4 bytes per row would have 16
-// rows in flight), which d lanes add from LDS while the next ones are loaded.
+// rows in flight), which d lanes add from LDS while the next ones are loaded.  The
+// occurrences may be of several bag blocks (unless `one`): put(k, sum, k') ends the sum of
+// block k, which block k' follows, and the last block's sum is returned.
 constexpr int kWaveLoads = 8;
 typedef float f4w __attribute__((ext_vector_type(4)));
 
-template <int D>
-__device__ __forceinline__ float wave_sum_span(const uint32_t* __restrict__ sval, uint32_t i0, uint32_t i1,
-                                               GradRows<D> gr, f4w* lds) {
+template <int D, typename Put>
+__device__ __forceinline__ float wave_sum_blocks(const uint32_t* __restrict__ sval, uint32_t i0, uint32_t i1,
+                                                 GradRows<D> gr, bool one, int nb_shift, f4w* lds, Put&& put) {
   static_assert(D <= 64, "one lane per column");
   constexpr int LPW = D / 4, RPI = 64 / LPW, R = RPI * kWaveLoads, NB = (R + 63) / 64;
   const int lane = threadIdx.x & 63;
   const float* lf = reinterpret_cast<const float*>(lds);
   f4w v[kWaveLoads];
+  uint32_t bag[NB];
   const auto load = [&](uint32_t at) {
-    uint32_t bag[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) bag[b] = sval[min(at + (uint32_t)(b * 64 + lane), i1 - 1)];
 #pragma unroll
@@ -1029,22 +1056,58 @@ __device__ __forceinline__ float wave_sum_span(const uint32_t* __restrict__ sval
   };
   load(i0);
   float acc = -0.0f;
+  uint32_t cur = __builtin_amdgcn_readfirstlane(bag[0]) >> nb_shift;
   for (uint32_t ic = i0; ic < i1; ic += R) {
 #pragma unroll
     for (int q = 0; q < kWaveLoads; ++q) lds[q * 64 + lane] = v[q];
     __builtin_amdgcn_wave_barrier();
+    uint32_t blk[NB];
+    uint64_t turn[NB];  // rows of the batch that are the first of a block
+    bool any = false;
+    if (!one) {  // (positions past the last occurrence repeat its bag)
+      uint32_t before = cur;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        blk[b] = bag[b] >> nb_shift;
+        const uint32_t p = __shfl_up(blk[b], 1);
+        turn[b] = __ballot(blk[b] != (lane == 0 ? before : p));
+        if (R < 64) turn[b] &= (1ull << (R & 63)) - 1;
+        before = __builtin_amdgcn_readlane(blk[b], 63);
+        any |= turn[b] != 0;
+      }
+    }
     if (ic + R < i1) load(ic + R);
     const int m = (int)min((uint32_t)R, i1 - ic);
-    if (lane < D) {
-      int r = 0;
-      for (; r + 8 <= m; r += 8) {
-        float x[8];
+    const auto add = [&](int r0, int r1) {
+      if (lane < D) {
+        int r = r0;
+        for (; r + 8 <= r1; r += 8) {
+          float x[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) x[q] = lf[(r + q) * D + lane];
+          for (int q = 0; q < 8; ++q) x[q] = lf[(r + q) * D + lane];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) acc = acc + x[q];
+          for (int q = 0; q < 8; ++q) acc = acc + x[q];
+        }
+        for (; r < r1; ++r) acc = acc + lf[r * D + lane];
       }
-      for (; r < m; ++r) acc = acc + lf[r * D + lane];
+    };
+    if (!any) {
+      add(0, m);
+    } else {
+      int r0 = 0;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        for (uint64_t left = turn[b]; left; left &= left - 1) {  // whole wave
+          const int j = (int)__builtin_ctzll(left), r1 = b * 64 + j;
+          add(r0, r1);
+          const uint32_t k = __builtin_amdgcn_readlane(blk[b], j);
+          put(cur, acc, k);
+          cur = k;
+          acc = -0.0f;
+          r0 = r1;
+        }
+      }
+      add(r0, m);
     }
     __builtin_amdgcn_wave_barrier();
   }
@@ -1068,6 +1131,140 @@ __device__ __forceinline__ uint32_t first_of_bag(const uint32_t* __restrict__ sv
   return a;
 }
 
+// The block sums of one window of a big row (e: the row, the window, the row's occurrences
+// [z, w)), and the flags that say which blocks of the row have a sum (the fold adds those).  A
+// window of one bag block searches its bounds; a window of kWindow occurrences takes the
+// blocks whose first occurrence lies in it, and the flags from its first block up to the next
+// window's.  With a window per block for every row, 1500 rows of 667 one-lookup bags were
+// 0.73M windows of one or two occurrences (a step of 1M lookups, 16 columns: 848 us, now
+// 261); with windows of occurrences for every row most windows of a row with many
+// occurrences per block were empty, and held up the others (100 tables of 80,000 lookups, 16
+// columns, two blocks: 873 us, now 643).
+template <int D>
+__device__ __forceinline__ void sum_window(const Work& w, const uint4& e, const uint32_t* __restrict__ sval,
+                                           GradRows<D> gr, int nblk, int nb_shift, f4w* lds) {
+  static_assert(kWindow == 64, "an occurrence per lane");
+  constexpr int GL = SumGeo<D>::GL, CL = SumGeo<D>::CL, U = 16;  // GL is 64 where runs are taken
+  const uint32_t lane = threadIdx.x & 63, l = lane & (GL - 1);
+  const uint32_t s0 = e.z, s1 = e.w;
+  uint32_t* fl = w.bbound + (int64_t)e.x * bound_stride(w.max_nblk);
+  float* bp = w.bpart + (int64_t)e.x * w.max_nblk * D;
+  uint32_t a, b, ka, kl, k_next;  // occurrences [a, b), blocks [ka, kl]; the flags up to k_next
+  if (block_windows(s1 - s0, nblk)) {
+    ka = kl = e.y;
+    k_next = ka + 1;
+    a = first_of_bag(sval, s0, s1, ka << nb_shift);
+    b = first_of_bag(sval, a, s1, k_next << nb_shift);
+    if (a == b) {
+      if (lane == 0) fl[ka] = 0;
+      return;
+    }
+  } else {
+    a = s0 + e.y * kWindow;
+    const uint32_t wend = min(a + kWindow, s1), n = wend - a;
+    // the window's blocks, one occurrence per lane, and those of the 64 after it
+    const uint32_t v = sval[min(a + lane, s1 - 1)] >> nb_shift, after = sval[min(wend + lane, s1 - 1)] >> nb_shift;
+    ka = __builtin_amdgcn_readfirstlane(v);
+    kl = __builtin_amdgcn_readlane(v, n - 1);
+    if (a > s0) {  // the block of the occurrence before belongs to an earlier window
+      const uint32_t before = sval[a - 1] >> nb_shift;
+      const uint64_t own = __ballot(lane < n && v != before);
+      if (own == 0) return;
+      const int first = (int)__builtin_ctzll(own);
+      a += (uint32_t)first;
+      ka = __builtin_amdgcn_readlane(v, first);
+    }
+    const uint64_t past = __ballot(wend + lane >= s1 || after != kl);
+    if (past) {
+      const int first = (int)__builtin_ctzll(past);
+      b = wend + (uint32_t)first;
+      k_next = b < s1 ? __builtin_amdgcn_readlane(after, first) : (uint32_t)nblk;
+    } else {
+      b = first_of_bag(sval, wend, s1, (kl + 1) << nb_shift);
+      k_next = b < s1 ? sval[b] >> nb_shift : (uint32_t)nblk;
+    }
+    if (a == s0)
+      for (uint32_t k = lane; k < ka; k += 64) fl[k] = 0;
+  }
+  float acc[CL];
+  const auto put = [&](uint32_t k, uint32_t next) {  // the sum of block k; no sums up to block `next`
+    if (lane < GL) {
+#pragma unroll
+      for (int c = 0; c < CL; ++c) bp[(int64_t)k * D + l * CL + c] = acc[c];
+    }
+    for (uint32_t j = k + lane; j < next; j += 64) fl[j] = j == k ? 1u : 0u;
+  };
+  const uint32_t bags = sval[b - 1] - sval[a] + 1;  // at most so many rows are loaded
+  if constexpr (D <= 64) {
+    if (D < 64 || b - a < 24 * bags) {
+      acc[0] = wave_sum_blocks<D>(sval, a, b, gr, ka == kl, nb_shift, lds, [&](uint32_t k, float sum, uint32_t next) {
+        acc[0] = sum;
+        put(k, next);
+      });
+      put(kl, k_next);
+      return;
+    }
+  } else if (ka == kl && b - a < 8 * bags) {
+    sum_span<D>(sval, a, b, gr, l, acc);
+    put(ka, k_next);
+    return;
+  }
+  // else run by run of occurrences in one bag, whose row is loaded once and added as often as
+  // the run is long, U runs in flight (with a load per occurrence the sum of a hot row is one
+  // chain of load latencies: 1024 bags of 488 lookups, 128 columns, 1490 us a step, now 782;
+  // the general path 957; at 4 occurrences of a row per bag a load each is ahead, 130 and 149)
+#pragma unroll
+  for (int c = 0; c < CL; ++c) acc[c] = -0.0f;
+  uint32_t cur = ka;
+  uint32_t next = sval[min(a + lane, b - 1)];
+  for (uint32_t ic = a; ic < b; ic += 64) {
+    const uint32_t my = next;
+    next = sval[min(ic + 64 + lane, b - 1)];
+    const int n = (int)min(64u, b - ic);
+    const uint32_t before = __shfl_up(my, 1);
+    uint64_t starts = __ballot((int)lane < n && (lane == 0 || my != before));
+    while (starts) {  // whole wave
+      int at[U + 1];
+      uint32_t bag[U];
+      float x[U][CL];
+#pragma unroll
+      for (int q = 0; q <= U; ++q) {
+        at[q] = starts ? (int)__builtin_ctzll(starts) : n;
+        if (q < U) starts &= starts - 1;  // (0 stays 0)
+      }
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        bag[q] = __builtin_amdgcn_readlane(my, min(at[q], n - 1));
+        const float* p = gr.row(bag[q]) + l * CL;
+#pragma unroll
+        for (int c = 0; c < CL; ++c) x[q][c] = p[c];
+      }
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        if (at[q] >= n) break;
+        const uint32_t k = bag[q] >> nb_shift;
+        if (k != cur) {
+          put(cur, k);
+          cur = k;
+#pragma unroll
+          for (int c = 0; c < CL; ++c) acc[c] = -0.0f;
+        }
+        int r = at[q + 1] - at[q];
+        for (; r >= 8; r -= 8) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int c = 0; c < CL; ++c) acc[c] = acc[c] + x[q][c];
+        }
+        for (; r > 0; --r)
+#pragma unroll
+          for (int c = 0; c < CL; ++c) acc[c] = acc[c] + x[q][c];
+      }
+    }
+  }
+  put(cur, k_next);
+}
+
 template <int D>
 __device__ __forceinline__ void sum_jobs(const Dev& dv, const Work& w, TabPrefix& P, const float* __restrict__ grad,
                                          const uint32_t* __restrict__ sval, int nblk, int nb_shift, int cshift, int wg,
@@ -1086,32 +1283,16 @@ __device__ __forceinline__ void sum_jobs(const Dev& dv, const Work& w, TabPrefix
 #pragma unroll
     for (int q = 0; q < CL; ++q) o[q] = acc[q];
   }
+  // then the windows of the big rows, a wave each
   __syncthreads();
-  tab_prefix(P, w.tab_info, dv.T, [](const TabInfo& x) { return x.big; });
-  const uint32_t nJ = P.pre[dv.T] * (uint32_t)nblk;
+  tab_prefix(P, w.tab_info, dv.T, [](const TabInfo& x) { return x.windows; });
+  const uint32_t nW = P.pre[dv.T];
   __shared__ f4w stage[D <= 64 ? 4 * kWaveLoads * 64 : 1];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (uint32_t j = (uint32_t)wg * 4 + wv; j < nJ; j += (uint32_t)nwg * 4) {
-    const uint32_t i = j / (uint32_t)nblk, k = j - i * (uint32_t)nblk;
+  const int wv = threadIdx.x >> 6;
+  for (uint32_t i = (uint32_t)wg * 4 + wv; i < nW; i += (uint32_t)nwg * 4) {
     const int t = tab_of(P, dv.T, i);
-    const uint32_t h = (w.tab_info[t].pos >> 9) + i - P.pre[t];
-    const uint4 m = w.umeta[w.big_rows[h]];
-    const uint32_t a = first_of_bag(sval, m.z, m.z + m.w, k << nb_shift);
-    const uint32_t b = first_of_bag(sval, a, m.z + m.w, (k + 1) << nb_shift);
-    // the fold adds the blocks whose flag is set
-    if (lane == 0) w.bbound[(int64_t)h * bound_stride(w.max_nblk) + k] = b > a ? 1u : 0u;
-    if (a == b) continue;
-    const GradRows gr = grad_rows<D>(grad, t, dv.T);
-    float* o = w.bpart + ((int64_t)h * w.max_nblk + k) * D;
-    if constexpr (D <= 64) {
-      const float acc = wave_sum_span<D>(sval, a, b, gr, stage + wv * kWaveLoads * 64);
-      if (lane < D) o[lane] = acc;
-    } else {
-      float acc[CL];
-      sum_span<D>(sval, a, b, gr, l, acc);
-#pragma unroll
-      for (int q = 0; q < CL; ++q) o[l * CL + q] = acc[q];
-    }
+    const uint4 e = w.big_window[(w.tab_info[t].pos >> kWindowShift) + i - P.pre[t]];
+    sum_window<D>(w, e, sval, grad_rows<D>(grad, t, dv.T), nblk, nb_shift, stage + (D <= 64 ? wv * kWaveLoads * 64 : 0));
   }
 }
 
@@ -1345,12 +1526,12 @@ hipError_t launch_backward_small(const Dev& d, const Work& w, const int32_t* idx
     if (e != hipSuccess) return e;
     if (decay && d.cnt) k_decay_small<<<grid_for(d.total_rows), 256, 0, s>>>(d.cnt, d.total_rows, w.tab_info, d.T);
     const auto rows = [&](auto kernel, int per) {
-      kernel<<<(unsigned)std::min<int64_t>((L + 256 * per - 1) / (256 * per), 1024), 256, 0, s>>>(d, w, sk, sval, step);
+      kernel<<<(unsigned)std::min<int64_t>((L + 256 * per - 1) / (256 * per), 1024), 256, 0, s>>>(d, w, sk, sval, step, nblk);
     };
     if (L < (1 << 19)) d.assoc <= 16 ? rows(k_mid_rows<16, 1>, 1) : rows(k_mid_rows<64, 1>, 1);
     else d.assoc <= 16 ? rows(k_mid_rows<16, 4>, 4) : rows(k_mid_rows<64, 4>, 4);
   } else {
-    k_front<<<(unsigned)d.T, kFrontThreads, 0, s>>>(d, w, idx, L, off, B, passes, G);
+    k_front<<<(unsigned)d.T, kFrontThreads, 0, s>>>(d, w, idx, L, off, B, passes, G, nblk);
     if (decay && d.cnt) k_decay_small<<<grid_for(d.total_rows), 256, 0, s>>>(d.cnt, d.total_rows, w.tab_info, d.T);
   }
   const uint32_t direct = mid ? kMidDirect : kSmallDirect;

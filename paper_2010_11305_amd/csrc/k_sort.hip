@@ -751,7 +751,7 @@ __global__ __launch_bounds__(256) void k_mid_begin(Dev dv, Work w, const int32_t
     if (t <= T) {
       sg.pos[t] = (uint32_t)p;
       sg.tbase[t] = run + ex;
-      if (t < T) w.tab_info[t] = TabInfo{(uint32_t)p, 0, 0, 0, 0, 0, 0, 0};
+      if (t < T) w.tab_info[t] = TabInfo{.pos = (uint32_t)p};
     }
     run += tot;
   }

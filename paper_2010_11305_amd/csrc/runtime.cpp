@@ -86,7 +86,7 @@ struct Plan {
   size_t o_rec, o_crow, o_tag, o_ts, o_cnt, o_accs, o_accr, o_desc, o_keyb, o_stats, o_err, state_bytes, table_bytes;
   // workspace offsets
   size_t o_kA, o_vA, o_kB, o_vB, o_ssmall, o_sst0, o_sst1, o_sseg, o_part, o_tcnt, o_tpre, o_uk, o_seg, o_setf, o_urow, o_utab, o_uslot,
-      o_uact, o_udest, o_umeta, o_ukey, o_nch, o_cbase, o_uvrow, o_uvu, o_partial, o_span, o_ubig, o_brows, o_bbound, o_bpart, o_tabf, o_src, o_ctr, o_tabi, ws_bytes;
+      o_uact, o_udest, o_umeta, o_ukey, o_nch, o_cbase, o_uvrow, o_uvu, o_partial, o_span, o_ubig, o_brows, o_bbound, o_bpart, o_tabf, o_src, o_ctr, o_tabi, o_bwin, ws_bytes;
   int64_t max_partials = 0;
   int64_t max_big = 0;
   int32_t max_nblk = 0;
@@ -229,6 +229,7 @@ int plan_config(const emb_cache_config* c, Plan* p) {
   p->o_src = take(4 * L);
   p->o_ctr = take(8 * embc::kNCounters);
   p->o_tabi = take(sizeof(embc::TabInfo) * (size_t)T);
+  p->o_bwin = take(16 * ((std::min(L, (size_t)embc::kMidLookupsMost) >> embc::kWindowShift) + 1));
   p->ws_bytes = o;
   return EMB_OK;
 }
@@ -462,6 +463,7 @@ int create_impl(const emb_cache_config* cfg, void* state, size_t state_bytes, vo
   w.fwd_src = reinterpret_cast<int32_t*>(wb + p.o_src);
   w.ctr = reinterpret_cast<unsigned long long*>(wb + p.o_ctr);
   w.tab_info = reinterpret_cast<embc::TabInfo*>(wb + p.o_tabi);
+  w.big_window = reinterpret_cast<uint4*>(wb + p.o_bwin);
   w.max_indices = cfg->max_indices;
   w.max_partials = p.max_partials;
 

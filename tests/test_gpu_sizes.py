@@ -261,3 +261,31 @@ def test_row_that_an_imported_cache_holds_twice(torch, batch, assoc, ways):
     assert np.all(c["crow"][ways[0]] == 3.0) and np.all(c["crow"][ways[1]] == 4.0)
     assert c["ts"][ways[0]] == 2 and c["ts"][ways[1]] == 9
     assert g.stats(0)["unique_hits"] == 1 and g.check() == 0
+
+
+WINDOWS = {
+    # rows past 512 lookups: one-lookup bags over many bag blocks (several windows per row, blocks
+    # without an occurrence between them), in a mid and in a small call
+    "sparse_d256": dict(rows=[20], dim=256, batch=20_000, pooling=("fixed", 1), zipf=1.05),
+    "sparse_d16": dict(rows=[40], dim=16, batch=60_000, pooling=("fixed", 1), zipf=1.05),
+    "sparse_small_d128": dict(rows=[9, 4, 9, 4, 9, 4, 9], dim=128, batch=7000, pooling=("fixed", 1), zipf=1.05),
+    "gaps_d64": dict(rows=[3000], dim=64, batch=100_000, pooling=("uniform", 0, 1), zipf=1.3),
+    # few long bags: runs of one bag, longer and shorter than a wave's batch of occurrences
+    "long_bags_d16": dict(rows=[50], dim=16, batch=5, pooling=("poisson", 9000), zipf=1.3),
+    "long_bags_d64": dict(rows=[50, 7], dim=64, batch=600, pooling=("poisson", 60), zipf=1.3),
+    "long_bags_d128": dict(rows=[30, 3], dim=128, batch=300, pooling=("poisson", 90), zipf=1.5),
+    "long_bags_small_d256": dict(rows=[12], dim=256, batch=140, pooling=("poisson", 50), zipf=1.2),
+    # more than 256 windows of 512: a row of some 150,000 lookups
+    "hottest_d32": dict(rows=[3], dim=32, batch=90_000, pooling=("fixed", 3), zipf=1.5),
+}
+
+
+@pytest.mark.parametrize("case", list(WINDOWS))
+def test_windows_of_big_rows(torch, case):
+    """The block sums of rows with more than 512 lookups, taken by windows of a row's lookups."""
+    cfg = custom_cfg(cache_fraction=0.2, assoc=2, **WINDOWS[case])
+    log(f"windows {case}")
+    idx, off = workload.make_indices(cfg, 0)
+    most = np.bincount(idx[:off[cfg["batch"]]]).max()
+    assert most > (131_072 if case == "hottest_d32" else 512)
+    steps(torch, cfg)
