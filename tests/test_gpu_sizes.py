@@ -120,6 +120,27 @@ MID = {
     # whole-key sort of many small tables; more than 64 tables in a workgroup's range
     "many_tables": dict(rows=[50 + 7 * (t % 11) for t in range(600)], dim=16, batch=48, pooling=("uniform", 0, 5),
                         cache_fraction=0.1, assoc=2, zipf=1.1),
+    # the unique rows of four per thread from 2^19 lookups on: just below and above, ragged tables of
+    # few and of many rows (workgroups across table boundaries), rows past 16 and 512 lookups
+    "below_2_19": dict(rows=[50_000, 7, 20_011, 300, 90_000], dim=16, batch=10_400, pooling=("uniform", 0, 20), zipf=1.1,
+                       cache_fraction=0.05, **LRU),
+    "above_2_19": dict(rows=[50_000, 7, 20_011, 300, 90_000], dim=16, batch=10_600, pooling=("uniform", 0, 20), zipf=1.1,
+                       cache_fraction=0.05, **LRU),
+    "above_2_19_lfu": dict(rows=[50_000, 7, 20_011, 300, 90_000], dim=32, batch=10_600, pooling=("uniform", 0, 20),
+                           zipf=1.1, cache_fraction=0.05, **LFU),
+    "above_2_19_64_ways": dict(rows=[90_000, 9, 3000], dim=16, batch=30_000, pooling=("uniform", 0, 12), zipf=1.1,
+                               cache_fraction=0.05, assoc=64, policy="lru"),
+    # 64 bags per wave of the expansion from 2^19 bags on: 26 tables, and one whose workgroups take
+    # several runs of 256 bags each (also below 2^19 bags, 16 per wave)
+    "many_bags_26": dict(rows=[3000 + 501 * t for t in range(26)], dim=16, batch=20_200, pooling=("uniform", 0, 2),
+                         zipf=1.1, cache_fraction=0.05, assoc=4, policy="lru"),
+    "many_bags_16": dict(rows=[90_000], dim=16, batch=300_001, pooling=("uniform", 0, 2), zipf=1.1, cache_fraction=0.05,
+                         **LFU),
+    "many_bags_64": dict(rows=[90_000], dim=16, batch=600_007, pooling=("uniform", 0, 2), zipf=1.1, cache_fraction=0.05,
+                         **LRU),
+    # past 2M lookups, below 2^18 per table
+    "above_2M": dict(rows=[20_000] * 10 + [60_000], dim=16, batch=16_001, pooling=("uniform", 6, 19), zipf=1.2,
+                     cache_fraction=0.05, **LRU),
     # both sides of the one-kernel forward
     "forward_below": dict(rows=[30_000, 700], dim=32, batch=13_107, pooling=("fixed", 9), zipf=1.2, cache_fraction=0.05,
                           assoc=16, policy="lru"),
