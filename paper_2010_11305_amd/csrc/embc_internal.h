@@ -26,6 +26,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "embc_route.h"
+
 namespace embc {
 
 constexpr uint32_t kKeyInvalid = 0xFFFFFFFFu;  // sort key of a skipped lookup (sorts last)
@@ -121,21 +123,6 @@ struct Dev {
   int64_t total_slots;
 };
 
-// Small calls (k_small.hip): three launches, in which one workgroup per table sorts the table's
-// lookups.  Measured steps (us), small against mid path and against the general one: 26
-// tables of 2048 lookups 47, 94 and 208, 16 of 3600: 79, 102 and 230, one of 8192: 62, 92
-// and 169; past 8192 lookups in a table its workgroup sorts in memory (one table of 20000:
-// 159, 98 and 161).  The host knows the number of lookups of all tables together, so the
-// line is drawn at 8192 per table on average and 65536 in all (nearly all of those in one
-// of many tables: 0.38 ms, 0.30 on the general path before the mid path was there).
-constexpr int64_t kSmallLookups = 65536;
-constexpr int64_t kSmallPerTable = 8192;
-constexpr int kSmallTables = 512;
-constexpr int32_t kSmallBags = 65536;
-constexpr bool small_call(int64_t L, int32_t B, int T) {
-  return L <= kSmallLookups && L <= kSmallPerTable * T && B <= kSmallBags && T <= kSmallTables;
-}
-
 // The lists of one table in a small or mid call, at offsets that follow from pos: unique rows
 // and sets from pos on, chunk sums from pos/8 (pos/16 in a mid call), big rows from pos/512, their
 // windows from pos/32.
@@ -151,18 +138,7 @@ struct TabInfo {
   uint32_t valid;   // the others (mid calls)
 };
 
-// Calls of moderate size (launch_mid_front, then as a small call): below 2M lookups, or 8M of
-// at most 2^18 per table.  Measured steps (us), mid against general path: 26 tables of 8192
-// lookups 125 and 247, 10 of 40000: 168 and 290, one of 1.2M (128 columns) 435 and 455, 100
-// of 30000: 592 and 960, 100 of 61000 (LFU) 1303 and 1438, 10 of 246000: 587 and 625; but 10
-// of 491000: 1040 and 917, 100 of 123000: 2396 and 2114 -- with that many lookups per table
-// the general path's gradient sums from LDS-staged bag blocks and its second stream win.
-constexpr int64_t kMidLookups = 1 << 21, kMidLookupsMost = 1 << 23, kMidPerTable = 1 << 18;
 constexpr int kMidWaves = 8192;  // waves of 64 bags from which on the expansion takes 64 bags per wave
-constexpr bool mid_call(int64_t L, int32_t B, int T) {
-  return L > 0 && B > 0 && T <= kSmallTables &&
-         (L < kMidLookups || (L < kMidLookupsMost && L <= kMidPerTable * T));
-}
 // Rows of up to this many lookups are summed by the update itself, and a chunk of the others
 // has at least one more; the chunk sums of a table start at pos >> shift.
 constexpr uint32_t kSmallDirect = 8, kMidDirect = 16;

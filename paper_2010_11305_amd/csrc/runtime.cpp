@@ -528,7 +528,7 @@ int emb_cache_backward_update(emb_cache_t h, const int32_t* indices, int64_t num
   const hipEvent_t* tev = nullptr;
   if (h->timing) tev = &h->tev[2 * (h->timed % emb_cache::kTimedCalls)];
   const bool small = embc::small_call(num_indices, batch, h->cfg.num_tables);
-  const bool mid = !small && embc::mid_call(num_indices, batch, h->cfg.num_tables);
+  const bool mid = !small && embc::mid_call(num_indices, batch, h->cfg.num_tables, h->cfg.dim);
   const hipError_t e =
       small || mid
             ? embc::launch_backward_small(h->dev, h->work, indices, num_indices, offsets, batch, grad_out, h->step,
