@@ -1144,7 +1144,7 @@ template <int D>
 __device__ __forceinline__ void sum_window(const Work& w, const uint4& e, const uint32_t* __restrict__ sval,
                                            GradRows<D> gr, int nblk, int nb_shift, f4w* lds) {
   static_assert(kWindow == 64, "an occurrence per lane");
-  constexpr int GL = SumGeo<D>::GL, CL = SumGeo<D>::CL, U = 16;  // GL is 64 where runs are taken
+  constexpr int GL = SumGeo<D>::GL, CL = SumGeo<D>::CL;  // GL is 64 where runs are taken
   const uint32_t lane = threadIdx.x & 63, l = lane & (GL - 1);
   const uint32_t s0 = e.z, s1 = e.w;
   uint32_t* fl = w.bbound + (int64_t)e.x * bound_stride(w.max_nblk);
@@ -1196,7 +1196,7 @@ __device__ __forceinline__ void sum_window(const Work& w, const uint4& e, const 
   };
   const uint32_t bags = sval[b - 1] - sval[a] + 1;  // at most so many rows are loaded
   if constexpr (D <= 64) {
-    if (D < 64 || b - a < 24 * bags) {
+    if (D < 64 || b - a < 16 * bags) {
       acc[0] = wave_sum_blocks<D>(sval, a, b, gr, ka == kl, nb_shift, lds, [&](uint32_t k, float sum, uint32_t next) {
         acc[0] = sum;
         put(k, next);
@@ -1210,9 +1210,10 @@ __device__ __forceinline__ void sum_window(const Work& w, const uint4& e, const 
     return;
   }
   // else run by run of occurrences in one bag, whose row is loaded once and added as often as
-  // the run is long, U runs in flight (with a load per occurrence the sum of a hot row is one
-  // chain of load latencies: 1024 bags of 488 lookups, 128 columns, 1490 us a step, now 782;
-  // the general path 957; at 4 occurrences of a row per bag a load each is ahead, 130 and 149)
+  // the run is long, up to 16 runs in flight (with a load per occurrence the sum of a hot row is
+  // one chain of load latencies: 1024 bags of 488 lookups, 128 columns, 1490 us a step, now 653,
+  // 64 columns 1536 and 1030; the general path 960 and 1268; but at 4 occurrences of a row per
+  // bag a load each is ahead, 130 and 149, and up to 32 columns the waves above always are)
 #pragma unroll
   for (int c = 0; c < CL; ++c) acc[c] = -0.0f;
   uint32_t cur = ka;
@@ -1223,7 +1224,8 @@ __device__ __forceinline__ void sum_window(const Work& w, const uint4& e, const 
     const int n = (int)min(64u, b - ic);
     const uint32_t before = __shfl_up(my, 1);
     uint64_t starts = __ballot((int)lane < n && (lane == 0 || my != before));
-    while (starts) {  // whole wave
+    const auto group = [&](auto runs) {  // the next U runs
+      constexpr int U = decltype(runs)::value;
       int at[U + 1];
       uint32_t bag[U];
       float x[U][CL];
@@ -1260,6 +1262,10 @@ __device__ __forceinline__ void sum_window(const Work& w, const uint4& e, const 
 #pragma unroll
           for (int c = 0; c < CL; ++c) acc[c] = acc[c] + x[q][c];
       }
+    };
+    while (starts) {  // whole wave
+      if (__popcll(starts) <= 4) group(std::integral_constant<int, 4>{});
+      else group(std::integral_constant<int, 16>{});
     }
   }
   put(cur, k_next);
