@@ -8,17 +8,30 @@ namespace embc {
 
 // Small calls (k_small.hip): three launches, in which one workgroup per table sorts the table's
 // lookups.  Measured steps (us), small against mid path and against the general one: 26
-// tables of 2048 lookups 47, 94 and 208, 16 of 3600: 79, 102 and 230, one of 8192: 62, 92
-// and 169; past 8192 lookups in a table its workgroup sorts in memory (one table of 20000:
-// 159, 98 and 161).  The host knows the number of lookups of all tables together, so the
-// line is drawn at 8192 per table on average and 65536 in all (nearly all of those in one
-// of many tables: 0.38 ms, 0.30 on the general path before the mid path was there).
+// tables of 2048 lookups 44, 84 and 211, 16 of 4000: 52, 91 and 174, one of 8000: 57, 83 and
+// 154.  Past 8192 lookups in a table its workgroup sorts in memory, and the host, which knows
+// the number of lookups of all tables together, cannot see that: with nearly all of them in
+// one of 8 tables, 12000 lookups take 105 us here, 86 and 150 there, 20000: 152, 94 and 157,
+// 65536: 374, 116 and 188 (one of 100 tables 377, 166 and 262), and 17000 of 2000 rows alone 161,
+// 83 and 149.  So the line is drawn at 8192 per table on average, and in all where one table
+// could hold them (12288 and 64 more per table: the general path's launches grow with the
+// tables), but at 65536 where the lookups are a multiple of a thousand bags or more: then the
+// bags have one length, and the tables one number of lookups (or, once in as many calls as
+// there are bags, they do not).
+// A set is decided by one group of lanes, row by row: 8000 rows of one set take 139 us, 88 and
+// 160; 17000 of 2048 rows 204, 96 and 157.  Past 8192 uneven lookups in all, tables with that
+// many rows per set (set_rows: of the table with the most) go to the mid path.
 constexpr int64_t kSmallLookups = 65536;
 constexpr int64_t kSmallPerTable = 8192;
+constexpr int64_t kSmallUneven = 12288, kSmallUnevenPerTable = 64, kSmallEvenBags = 1024, kSmallSetRows = 1024;
 constexpr int kSmallTables = 512;
 constexpr int32_t kSmallBags = 65536;
-constexpr bool small_call(int64_t L, int32_t B, int T) {
-  return L <= kSmallLookups && L <= kSmallPerTable * T && B <= kSmallBags && T <= kSmallTables;
+constexpr bool small_call(int64_t L, int32_t B, int T, int64_t set_rows) {
+  if (L > kSmallLookups || L > kSmallPerTable * T || B > kSmallBags || T > kSmallTables) return false;
+  if (L <= kSmallPerTable) return true;
+  const int64_t bags = (int64_t)T * B;
+  if (bags >= kSmallEvenBags && L % bags == 0) return true;
+  return L <= kSmallUneven + kSmallUnevenPerTable * T && set_rows <= kSmallSetRows;
 }
 
 // Calls of moderate size (launch_mid_front, then as a small call): below 2M lookups, or 8M of at

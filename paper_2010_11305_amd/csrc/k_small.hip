@@ -1524,7 +1524,7 @@ hipError_t launch_backward_small(const Dev& d, const Work& w, const int32_t* idx
   const int G = d.assoc <= 16 ? 16 : d.assoc <= 32 ? 32 : 64;
   const int nb_shift = __builtin_ctz((unsigned)(kBlockFloats / d.dim));
   const int nblk = (int)(((int64_t)B + (kBlockFloats / d.dim) - 1) >> nb_shift);
-  if (nblk > w.max_nblk || !(mid ? mid_call(L, B, d.T, d.dim) : small_call(L, B, d.T))) return hipErrorInvalidValue;
+  if (nblk > w.max_nblk || d.T > kSmallTables || L > (mid ? kMidLookupsMost : kSmallLookups)) return hipErrorInvalidValue;
   const uint32_t* sval = w.valsB;
   if (mid) {
     const uint32_t* sk = nullptr;

@@ -245,6 +245,7 @@ struct emb_cache {
   uint64_t step = 0;
   int key_bits = 1;
   int local_passes = 1;  // digit passes of the largest table's local keys
+  int64_t set_rows = 0;  // most rows that share a set
   int seg_passes = 0;  // digit passes of the per-table sort, 0 = sort the whole key
   // measurement: event pairs around the row-update kernel of the last kTimedCalls calls
   static constexpr int kTimedCalls = 64;
@@ -387,7 +388,10 @@ int create_impl(const emb_cache_config* cfg, void* state, size_t state_bytes, vo
   // takes fewer passes when every table's key range is much smaller than their sum
   {
     int64_t max_range = 1;
-    for (int t = 0; t < cfg->num_tables; ++t) max_range = std::max(max_range, p.key_base[t + 1] - p.key_base[t]);
+    for (int t = 0; t < cfg->num_tables; ++t) {
+      max_range = std::max(max_range, p.key_base[t + 1] - p.key_base[t]);
+      if (p.desc[t].n_sets > 0) h->set_rows = std::max(h->set_rows, p.desc[t].Q);
+    }
     const int seg = (bit_length((uint64_t)max_range) + 7) / 8;
     h->local_passes = seg;
     h->seg_passes = seg < (h->key_bits + 7) / 8 ? seg : 0;
@@ -527,7 +531,7 @@ int emb_cache_backward_update(emb_cache_t h, const int32_t* indices, int64_t num
   const bool decay = h->cfg.policy == EMB_LFU && K > 0 && h->step > 0 && h->step % (uint64_t)K == 0;
   const hipEvent_t* tev = nullptr;
   if (h->timing) tev = &h->tev[2 * (h->timed % emb_cache::kTimedCalls)];
-  const bool small = embc::small_call(num_indices, batch, h->cfg.num_tables);
+  const bool small = embc::small_call(num_indices, batch, h->cfg.num_tables, h->set_rows);
   const bool mid = !small && embc::mid_call(num_indices, batch, h->cfg.num_tables, h->cfg.dim);
   const hipError_t e =
       small || mid

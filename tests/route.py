@@ -5,13 +5,15 @@ import os
 import subprocess
 import tempfile
 
+import numpy as np
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2010_11305_amd", "csrc")
 
 SOURCE = """
 #include "embc_route.h"
-extern "C" int route(int64_t L, int32_t B, int T, int dim) {
-  return embc::small_call(L, B, T) ? 0 : embc::mid_call(L, B, T, dim) ? 1 : 2;
+extern "C" int route(int64_t L, int32_t B, int T, int dim, int64_t set_rows) {
+  return embc::small_call(L, B, T, set_rows) ? 0 : embc::mid_call(L, B, T, dim) ? 1 : 2;
 }
 """
 
@@ -26,8 +28,15 @@ def _lib():
         return ctypes.CDLL(so)
 
 
+def set_rows(cfg):
+    """The most rows of a table that share a set (0 without a cache)."""
+    frac, assoc = cfg.get("cache_fraction", 0.0), cfg.get("assoc", 1)
+    return max(-(-n // max(1, int(np.floor(frac * n)) // assoc)) for n in cfg["rows"]) if frac > 0 else 0
+
+
 def route(cfg, lookups, batch=None):
     """"small", "mid" or "general" for a call of `lookups` on the tables of cfg."""
     B = cfg["batch"] if batch is None else batch
-    r = _lib().route(ctypes.c_int64(int(lookups)), int(B), len(cfg["rows"]), int(cfg["dim"]))
+    r = _lib().route(ctypes.c_int64(int(lookups)), int(B), len(cfg["rows"]), int(cfg["dim"]),
+                     ctypes.c_int64(set_rows(cfg)))
     return ("small", "mid", "general")[r]

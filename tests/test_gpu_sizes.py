@@ -1,7 +1,7 @@
 """GPU parity at the sizes where a call changes its route: the three-launch step of small calls
 (one workgroup per table: 1024 to 8192 keys in LDS, more in memory) up to 65536 lookups, 8192
-per table on average and 512 tables; the mid step up to 2M lookups; the general step above
-either; and the forward in one kernel below 2^18 lookups.  Every piece of state, statistic
+per table on average and 512 tables; the mid step up to 2M lookups (and some of up to 8M); the
+general step above either; and the forward in one kernel below 2^18 lookups.  Every piece of state, statistic
 and pooled output equals the oracle's bit for bit."""
 import numpy as np
 import pytest
@@ -9,6 +9,7 @@ import pytest
 from common import custom_cfg
 from paper_2010_11305_amd import workload
 from parity import compare_state, log, make_pair, step_both
+from route import route
 
 pytestmark = pytest.mark.gpu
 
@@ -85,8 +86,8 @@ def test_sets_with_more_rows_than_lanes(torch, assoc, policy):
 
 @pytest.mark.parametrize("T", [4, 6])
 def test_one_table_holds_all_lookups(torch, T):
-    """Six tables of which one has 40000 lookups (a small call, sorted in memory by tiles; the
-    same from four tables on is a mid call) in three bags of many repeats, the others a few."""
+    """Four or six tables of which one has 40000 lookups (too many for a small call of so few tables)
+    in three bags of many repeats, the others a few."""
     cfg = custom_cfg(rows=[5000, 300, 7000, 9, 20, 20][:T], batch=3, dim=32, **LRU)
     o, g = make_pair(cfg, max_indices=50_000)
     rng = np.random.default_rng(5)
@@ -310,3 +311,80 @@ def test_windows_of_big_rows(torch, case):
     most = np.bincount(idx[:off[cfg["batch"]]]).max()
     assert most > (131_072 if case == "hottest_d32" else 512)
     steps(torch, cfg)
+
+
+def skewed(rng, cfg, counts, zipf):
+    """A batch with counts[t] lookups in table t, in bags of random sizes (some empty), a few of
+    them out of range, and a few positions outside every bag."""
+    B, off, idx = cfg["batch"], [3], [np.array([1, 2, -9], np.int32)]
+    for n, rows in zip(counts, cfg["rows"]):
+        cuts = np.sort(rng.integers(0, n + 1, B - 1))
+        off += (off[-1] + np.append(cuts, n)).tolist()
+        r = np.minimum(rng.zipf(zipf, n) - 1, 2**31 - 1).astype(np.int64)
+        r = ((r * 7919 + 11) % rows).astype(np.int32)
+        r[rng.random(n) < 0.002] = rows
+        idx.append(r)
+    idx.append(np.array([5], np.int32))
+    return {"indices": np.concatenate(idx), "offsets": np.array(off, np.int32), "batch": B,
+            "grad": rng.standard_normal((B, len(counts), cfg["dim"])).astype(np.float32)}
+
+
+LARGE = {
+    # (configuration, lookups per table, Zipf): small calls with tables of more than 8192 lookups
+    "lru": (dict(rows=[300_000] + [40] * 7, dim=32, batch=900, cache_fraction=0.02, **LRU), [12_000] + [9] * 7, 1.2),
+    "one_lookup_bags": (dict(rows=[70_000] + [40] * 7, batch=12_001, cache_fraction=0.02, **LRU), [12_000] + [9] * 7, 1.2),
+    "lfu": (dict(rows=[5, 60_000, 300], dim=16, batch=700, cache_fraction=0.05, **LFU), [11, 11_900, 500], 1.3),
+    "direct": (dict(rows=[60_000, 50], dim=128, batch=77, cache_fraction=0.05, **DIRECT), [12_000, 300], 1.3),
+    "no_cache": (dict(rows=[60_000, 50], dim=16, batch=700, cache_fraction=0.0), [12_000, 300], 1.3),
+    "one_set": (dict(rows=[1000, 50, 3], batch=400, cache_fraction=1e-6, assoc=16, policy="lru"), [11_900, 300, 200], 1.1),
+    "hot_row": (dict(rows=[200_000, 50, 3, 8], batch=400, cache_fraction=0.02, assoc=16, policy="lfu"),
+                [10_000, 300, 200, 2000], 2.5),
+    "three_rows": (dict(rows=[3, 50], batch=400, cache_fraction=0.5, assoc=1, policy="lru"), [12_000, 300], 1.5),
+    "n_8193": (dict(rows=[50_000, 50], batch=64, cache_fraction=0.02, **LRU), [8193, 8], 1.2),
+    "one_bag": (dict(rows=[50_000, 50, 7], batch=1, cache_fraction=0.02, **LRU), [12_288, 8, 100], 1.2),
+    "two_large": (dict(rows=[50_000, 60_000] + [40] * 98, dim=64, batch=300, cache_fraction=0.02, **LRU),
+                  [8200, 8300] + [9] * 98, 1.2),
+    "five_tiles": (dict(rows=[9] * 511 + [50_000], batch=60, cache_fraction=0.02, **LRU), [3] * 511 + [43_000], 1.2),
+}
+
+
+@pytest.mark.parametrize("case", list(LARGE))
+def test_large_tables_of_small_calls(torch, case):
+    """Tables of a small call with more lookups than the LDS holds, sorted in memory by tiles."""
+    kw, counts, zipf = LARGE[case]
+    cfg = custom_cfg(**kw)
+    rng = np.random.default_rng(len(case))
+    log(f"large table {case}")
+    o, g = make_pair(cfg, max_indices=sum(counts) + 4)
+    assert max(counts) > 8192 and route(cfg, sum(counts) + 4) == "small"
+    for k in range(3):
+        step_both(o, g, cfg, skewed(rng, cfg, counts if k != 1 else counts[::-1], zipf), torch)
+        compare_state(o, g, cfg)
+    # a bad offset inside the large table rejects the call
+    t = int(np.argmax(counts))
+    if cfg["batch"] > 2:
+        st = skewed(rng, cfg, counts, zipf)
+        st["offsets"][t * cfg["batch"] + cfg["batch"] // 2] += 10**6
+        dev = [torch.from_numpy(st[k]).cuda() for k in ("indices", "offsets", "grad")]
+        g.check()
+        g.backward_update(dev[0], dev[1], cfg["batch"], dev[2])
+        assert o.backward_update(st["indices"], st["offsets"], cfg["batch"], st["grad"])
+        torch.cuda.synchronize()
+        from paper_2010_11305_amd import emb_cache as ec
+        assert g.check() == ec.EMB_EINDEX and g.stats(t)["unique"] == 0
+        compare_state(o, g, cfg)
+
+
+@pytest.mark.parametrize("even", [True, False])
+def test_uneven_tables_take_the_mid_route(torch, even):
+    """65536 lookups of eight tables in 128 bags each: a small call, where their number is a
+    multiple of the bags (also when one table holds nearly all: sorted in memory), else a mid one."""
+    cfg = custom_cfg(rows=[60_000] + [500] * 7, batch=128, cache_fraction=0.02, **LRU)
+    rng = np.random.default_rng(8)
+    for counts in ([8192] * 8, [65_004, 500, 0, 1, 2, 3, 6, 20]):
+        counts = [counts[0] - 4 if even else counts[0] - 5] + counts[1:]
+        st = skewed(rng, cfg, counts, 1.2)
+        o, g = make_pair(cfg, max_indices=70_000)
+        assert route(cfg, st["indices"].size) == ("small" if even else "mid")
+        step_both(o, g, cfg, st, torch)
+        compare_state(o, g, cfg)
