@@ -1,5 +1,5 @@
-// Which of the three routes a backward call takes, by its sizes: for the runtime, and for a host
-// compiler.
+// Which of the three routes a backward call takes, and which of the two a forward call, by its
+// sizes: for the launches, and for a host compiler.
 #pragma once
 
 #include <stdint.h>
@@ -51,6 +51,28 @@ constexpr bool mid_call(int64_t L, int32_t B, int T, int dim) {
   if (L <= 0 || B <= 0 || T > kSmallTables) return false;
   if (L < kMidLookups) return true;
   return L < kMidLookupsMost && L <= kMidPerTable * T && (L * dim <= kMidColumnsPerTable * T || L * dim <= kMidColumns);
+}
+
+// A forward of one kernel (k_fwd_fused) or of two, the probe and the gather.  From 2^18 lookups on the
+// chip is full and two are faster.  Below (us, one kernel against two, 26 tables):
+// - A row's group has few lanes to probe a long bag, the fewer the narrower the row.  16 columns: one
+//   is ahead with 8 lookups per bag; 60: 37 and 34, 300: 139 and 108 (4 ways), 190 and 109 (32).
+//   32 columns: up to 16 ways one is ahead or within 15% either way; 32 ways, one table of 1000
+//   200-lookup bags 95 and 107, of four 750-lookup bags 276 and 219.  64 columns, 32 ways: 81 and
+//   106, 225 and 209.
+// - In a short bag of wide rows most lanes of a group wait for the few that probe, which matters
+//   once the chip is full, and more for sets of several lines.  Up to 16 ways: 64 columns are
+//   ahead throughout; 128 columns of one-lookup bags, 53000 lookups ahead, 213000: 39 and 33;
+//   256 columns, 53000: 22 and 22, 213000: 66 and 54 (in 30-lookup bags 25 and 27).  From 32 ways
+//   on: 64 columns, 53000 ahead, 213000: 40 and 31 (in 30-lookup bags 27 and 29); 128 columns,
+//   27000 ahead, 213000: 68 and 35 (27 and 30); 256 columns, 27000: 22 and 20, 213000: 122 and 57
+//   (41 and 30; 100000 in 60-lookup bags 32 and 36).
+constexpr int64_t kFusedBelow = 1 << 18;
+constexpr bool fused_call(int64_t L, int64_t nbags, int dim, int assoc) {
+  const bool many = assoc > 16;
+  const int64_t longest = dim == 16 ? 8 : dim == 32 && many ? 256 : kFusedBelow;  // lookups per bag
+  if (L >= kFusedBelow || L > longest * nbags) return false;
+  return many ? L * dim <= 7 << 19 || nbags * dim <= 7 << 17 : dim <= 64 || L * dim <= 3 << 22 || nbags * dim <= 1 << 21;
 }
 
 }  // namespace embc

@@ -403,7 +403,6 @@ __global__ __launch_bounds__(256) void k_fwd_begin(Dev dv, const int32_t* __rest
 // Bags are taken flat, table-major, in one contiguous range per XCD and per workgroup, so
 // that a workgroup meets few tables and every XCD has the same number of bags.
 constexpr int kFusedUnroll = 4;  // rows in flight per row group
-constexpr int64_t kFusedBelow = 1 << 18;  // lookups per call
 
 template <int D, int BITS, bool SB16, int MAXA>
 __global__ __launch_bounds__(256) void k_fwd_fused(Dev dv, const int32_t* __restrict__ idx, int64_t L,
@@ -538,9 +537,7 @@ hipError_t launch_forward(const Dev& d, const Work& w, const int32_t* idx, int64
   const int64_t nbags = (int64_t)d.T * B;
   k_fwd_begin<<<grid_for(nbags, 2048), 256, 0, s>>>(d, off, nbags, L);
   if (nbags == 0) return hipGetLastError();
-  // (a narrow row's group has few lanes to probe a long bag: one table of 1000 50-lookup bags of
-  // 16 columns takes 61 us in one kernel and 39 in two; at 32 columns one kernel is ahead)
-  if (L < kFusedBelow && (d.dim > 16 || L <= 8 * nbags)) {
+  if (fused_call(L, nbags, d.dim, d.assoc)) {
     const DivConst byB = div_const((uint32_t)B);
     return dispatch_row(d.dim, d.bits, d.sb16, [&]<int D, int BITS, bool SB16>() -> hipError_t {
       // (few bags are spread over 512 workgroups)

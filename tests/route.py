@@ -1,4 +1,4 @@
-"""The route a backward call takes: the library's own rule (embc_route.h), compiled for the host."""
+"""The route a backward or forward call takes: the library's own rule (embc_route.h), compiled for the host."""
 import ctypes
 import functools
 import os
@@ -15,6 +15,7 @@ SOURCE = """
 extern "C" int route(int64_t L, int32_t B, int T, int dim, int64_t set_rows) {
   return embc::small_call(L, B, T, set_rows) ? 0 : embc::mid_call(L, B, T, dim) ? 1 : 2;
 }
+extern "C" int fused(int64_t L, int64_t nbags, int dim, int assoc) { return embc::fused_call(L, nbags, dim, assoc); }
 """
 
 
@@ -40,3 +41,8 @@ def route(cfg, lookups, batch=None):
     r = _lib().route(ctypes.c_int64(int(lookups)), int(B), len(cfg["rows"]), int(cfg["dim"]),
                      ctypes.c_int64(set_rows(cfg)))
     return ("small", "mid", "general")[r]
+
+
+def one_kernel_forward(cfg, lookups):
+    return bool(_lib().fused(ctypes.c_int64(int(lookups)), ctypes.c_int64(cfg["batch"] * len(cfg["rows"])),
+                             int(cfg["dim"]), int(cfg["assoc"])))

@@ -9,7 +9,7 @@ import pytest
 from common import custom_cfg
 from paper_2010_11305_amd import workload
 from parity import compare_state, log, make_pair, step_both
-from route import route
+from route import one_kernel_forward, route
 
 pytestmark = pytest.mark.gpu
 
@@ -388,3 +388,16 @@ def test_uneven_tables_take_the_mid_route(torch, even):
         assert route(cfg, st["indices"].size) == ("small" if even else "mid")
         step_both(o, g, cfg, st, torch)
         compare_state(o, g, cfg)
+
+
+@pytest.mark.parametrize("dim,assoc,batch,lookups", [
+    (16, 4, 50, 8), (32, 64, 20, 256), (64, 32, 28_672, 1), (128, 32, 14_336, 1),
+    (256, 64, 7168, 1), (128, 8, 49_152, 1), (256, 16, 24_576, 1)])
+def test_forward_of_one_and_two_kernels(torch, dim, assoc, batch, lookups):
+    """Forwards on both sides of the lines between one kernel and two (two tables, fixed bags)."""
+    for m, B, one in ((lookups, batch, True), ((lookups + 1, batch, False) if lookups > 1 else (1, batch + 1, False))):
+        cfg = custom_cfg(rows=[5000, 300], dim=dim, assoc=assoc, batch=B, pooling=("fixed", m), cache_fraction=0.2,
+                         zipf=1.2, bits=8)
+        log(f"forward d{dim} {assoc} ways, {B} bags of {m}")
+        assert one_kernel_forward(cfg, 2 * B * m) == one
+        steps(torch, cfg)
