@@ -206,7 +206,7 @@ enum : int {
   kCScanTotal = 6,  // scratch total of the last scan
   kCBadOffsets = 7, // offsets of this step failed validation
   kCBig = 8,        // big rows
-  kCHitEv = 9,      // inserts displacing a resident updated this step
+  kCHitEv = 9,      // 1: some insert displaces a resident updated this step
   kNCounters = 16
 };
 

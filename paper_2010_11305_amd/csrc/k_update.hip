@@ -22,7 +22,11 @@
 
 namespace embc {
 
-constexpr int64_t kSpreadBelow = 1 << 21;  // lookups per step below which SPREAD kernels run
+// Lookups per step below which the SPREAD kernels run: only calls of more tables than the small
+// and mid routes take (512) come here with so few.  Measured steps (us), SPREAD against not: 600
+// tables of 200 lookups, 16 columns 319 and 805, 128 columns 363 and 594; of 3000: 720 and 1634,
+// 1486 and 1908; 5000 tables of 300 lookups, 128 columns 2834 and 10306.
+constexpr int64_t kSpreadBelow = 1 << 21;
 
 __global__ __launch_bounds__(256) void k_bwd_begin(Dev dv, unsigned long long* ctr, int64_t L) {
   zero_stats(dv, kStBwdLookups, kStHitEvictions);
@@ -944,8 +948,8 @@ hipError_t launch_backward(const Dev& d, const Work& w, const int32_t* idx, int6
   const int nb_shift = __builtin_ctz((unsigned)(kBlockFloats / d.dim));
   const int stage_shift = nb_shift - __builtin_ctz((unsigned)kStages);
   const int nblk = (int)(((int64_t)B + (kBlockFloats / d.dim) - 1) / (kBlockFloats / d.dim));
-  // a small step spreads its tables' rows over all row groups (a larger one has more rows
-  // per table than groups anyway, and keeps the kernels with fewer registers)
+  // a step of few lookups per table spreads its tables' rows over all row groups (a larger one has
+  // more rows per table than groups anyway, and keeps the kernels with fewer registers)
   const bool spread = L < kSpreadBelow;
   if (nblk > w.max_nblk) return hipErrorInvalidValue;
   if (nblk > 0) k_block_bounds<<<grid(k_block_bounds), 256, 0, s>>>(w, sv, stage_shift, nblk);
@@ -955,21 +959,16 @@ hipError_t launch_backward(const Dev& d, const Work& w, const int32_t* idx, int6
     // packing of the row update's inputs on the side stream, after the decisions: the
     // block sums beside the eviction 1111 -> 1434 us)
     const bool cached = d.total_slots > 0;
-    const hipStream_t s2 = side.s;
     if (cached) {
-      if (s2 != s) {
-        hipError_t e2 = hipEventRecord(side.fork, s);
-        if (e2 == hipSuccess) e2 = hipStreamWaitEvent(s2, side.fork, 0);
-        if (e2 != hipSuccess) return e2;
-      }
-      if (d.assoc <= 16) k_policy<16><<<grid(k_policy<16>), 256, 0, s2>>>(d, w, step);
-      else if (d.assoc <= 32) k_policy<32><<<grid(k_policy<32>), 256, 0, s2>>>(d, w, step);
-      else k_policy<64><<<grid(k_policy<64>), 256, 0, s2>>>(d, w, step);
-      k_evict<D, BITS, SB16, false><<<grid(k_evict<D, BITS, SB16, false>), 256, 0, s2>>>(d, w, sv, grad, step);
-      if (s2 != s) {
-        const hipError_t e2 = hipEventRecord(side.join, s2);
-        if (e2 != hipSuccess) return e2;
-      }
+      hipError_t e2 = hipEventRecord(side.fork, s);
+      if (e2 == hipSuccess) e2 = hipStreamWaitEvent(side.s, side.fork, 0);
+      if (e2 != hipSuccess) return e2;
+      if (d.assoc <= 16) k_policy<16><<<grid(k_policy<16>), 256, 0, side.s>>>(d, w, step);
+      else if (d.assoc <= 32) k_policy<32><<<grid(k_policy<32>), 256, 0, side.s>>>(d, w, step);
+      else k_policy<64><<<grid(k_policy<64>), 256, 0, side.s>>>(d, w, step);
+      k_evict<D, BITS, SB16, false><<<grid(k_evict<D, BITS, SB16, false>), 256, 0, side.s>>>(d, w, sv, grad, step);
+      e2 = hipEventRecord(side.join, side.s);
+      if (e2 != hipSuccess) return e2;
     }
     if (spread) k_partials<D, true><<<grid(k_partials<D, true>), 256, 0, s>>>(d, w, sv, grad);
     else k_partials<D, false><<<grid(k_partials<D, false>), 256, 0, s>>>(d, w, sv, grad);
@@ -979,10 +978,8 @@ hipError_t launch_backward(const Dev& d, const Work& w, const int32_t* idx, int6
       k_block_fold<D><<<grid(k_block_fold<D>), 256, 0, s>>>(w, nblk);
     }
     if (cached) {
-      if (s2 != s) {
-        const hipError_t e2 = hipStreamWaitEvent(s, side.join, 0);
-        if (e2 != hipSuccess) return e2;
-      }
+      const hipError_t e2 = hipStreamWaitEvent(s, side.join, 0);
+      if (e2 != hipSuccess) return e2;
       // a resident hit this step is displaced only under LFU or in a direct-mapped LRU
       // cache (under LRU a hit takes the step's stamp, which no candidate exceeds)
       if (d.policy != 0 || d.assoc == 1)
