@@ -185,10 +185,10 @@ int emb_cache_forward(emb_cache_t h, const int32_t* indices, int64_t num_indices
 /* Forward for callers that cannot allocate device memory or pass a workspace:
  * code under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation.  Same computation, results and statistics as emb_cache_forward,
- * but the per-call temporaries (one code per lookup and a few counter words)
- * live in a static device array owned by the library, EMB_NOALLOC_SCRATCH_BYTES
- * (64 MiB) per GPU, instead of the handle's workspace; the call allocates
- * nothing and calls no allocating routine.  num_indices may be at most
+ * but the per-call temporaries (one code per lookup) live in a static device
+ * array owned by the library, EMB_NOALLOC_SCRATCH_BYTES (64 MiB) per GPU,
+ * instead of the handle's workspace; the call allocates nothing and calls no
+ * allocating routine.  num_indices may be at most
  * EMB_NOALLOC_MAX_INDICES; beyond it the call returns EMB_ENOMEM and enqueues
  * nothing (max_indices of the handle does not apply).  Each GPU the library
  * runs on holds its own copy of the array from the first handle created on it

@@ -580,7 +580,7 @@ hipError_t launch_forward(const Dev& d, const Work& w, const int32_t* idx, int64
     // few bags are spread over 512 workgroups (16 long bags in one wave take 449 us, 344 on 8
     // workgroups)
     int tile_bags = 256 / Geo<D>::LPR;
-    while (tile_bags > 1 && (int64_t)d.T * ((B + tile_bags - 1) / tile_bags) < 512) tile_bags /= 2;
+    while (tile_bags > 1 && d.T * (((int64_t)B + tile_bags - 1) / tile_bags) < 512) tile_bags /= 2;
     const DivConst per_table = div_const((uint32_t)(((int64_t)B + tile_bags - 1) / tile_bags));
     const int64_t tiles = (int64_t)per_table.d * d.T;
     const int64_t cap = resident_grid(reinterpret_cast<const void*>(k_fwd_gather<D, BITS, SB16>));
@@ -591,15 +591,14 @@ hipError_t launch_forward(const Dev& d, const Work& w, const int32_t* idx, int64
 }
 
 // ---- forward without a workspace ---------------------------------------------------------
-// For callers that cannot allocate: the forward's per-call temporaries (the counter words
-// written by the offset check, then one code per lookup) live in `scratch`, a static
-// device array that every GPU the library runs on holds until the process ends.  Host
-// code never passes the array's name to a kernel (on the host it is only a stand-in): it
-// passes the device address that hipGetSymbolAddress returns for the current device,
-// looked up once per device.
+// For callers that cannot allocate: the forward's per-call temporaries (one code per lookup) live
+// in `scratch`, a static device array that every GPU the library runs on holds until the
+// process ends; its first kNoAllocHeader bytes are not used (EMB_NOALLOC_MAX_INDICES leaves
+// them out).  Host code never passes the array's name to a kernel (on the host it is only a
+// stand-in): it passes the device address that hipGetSymbolAddress returns for the current
+// device, looked up once per device.
 constexpr size_t kNoAllocHeader = 256;
 static_assert(EMB_NOALLOC_MAX_INDICES == (EMB_NOALLOC_SCRATCH_BYTES - kNoAllocHeader) / 4, "scratch layout");
-static_assert(kNCounters * sizeof(unsigned long long) <= kNoAllocHeader, "counter words");
 static __device__ __align__(256) uint8_t scratch[EMB_NOALLOC_SCRATCH_BYTES];
 
 hipError_t noalloc_scratch(uint8_t** out) {
@@ -626,9 +625,8 @@ hipError_t launch_forward_noalloc(const Dev& d, uint8_t* scratch_dev, const int3
                                   const int32_t* off, int32_t B, float* out, hipStream_t s) {
   if (scratch_dev == nullptr || L < 0 || L > EMB_NOALLOC_MAX_INDICES) return hipErrorInvalidValue;
   // the same kernels as launch_forward; nothing in the scratch is read before it is written
-  // in the same call (the counter words are only written), so it needs no clearing
+  // in the same call, so it needs no clearing
   Work w{};
-  w.ctr = reinterpret_cast<unsigned long long*>(scratch_dev);
   w.fwd_src = reinterpret_cast<int32_t*>(scratch_dev + kNoAllocHeader);
   w.max_indices = EMB_NOALLOC_MAX_INDICES;
   return launch_forward(d, w, idx, L, off, B, out, s);
