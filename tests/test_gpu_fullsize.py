@@ -15,7 +15,8 @@ import pytest
 
 from common import oracle_from_cfg
 from exact import dequant_exact
-from parity import assert_f32, assert_same, compare_state, log
+from parity import assert_f32, assert_same, compare_state, log, make_pair, step_both
+from route import route
 from paper_2010_11305_amd import configs, workload
 
 pytestmark = pytest.mark.gpu
@@ -138,16 +139,45 @@ def test_stress_full_size_properties(torch):
     assert g.check() == 0
 
 
-def test_stress_row_slice_parity(torch):
+@pytest.mark.parametrize("batch,steps,want", [(4096, 4, "mid"), (32_800, 2, "general")])
+def test_stress_row_slice_parity(torch, batch, steps, want):
+    """The general route is the one the full workload takes."""
     from paper_2010_11305_amd.emb_cache import EmbCache
-    cfg = configs.get("stress", rows=[2_000_000], batch=4096)
-    log("stress slice: 2M rows x d256 INT8, 32-way LRU, SR")
+    cfg = configs.get("stress", rows=[2_000_000], batch=batch)
+    log(f"stress slice: 2M rows x d256 INT8, 32-way LRU, SR, {batch} bags ({want})")
+    assert route(configs.get("stress"), 64 * 65536) == "general" and route(cfg, 64 * batch) == want
     o = oracle_from_cfg(cfg)
     o.init_uniform(cfg["init_lo"], cfg["init_hi"], cfg["init_seed"])
-    st = [workload.make_step(cfg, k) for k in range(4)]
+    st = [workload.make_step(cfg, k) for k in range(steps)]
     g = EmbCache(cfg, max_indices=max(s["indices"].size for s in st))
     g.init_uniform(cfg["init_lo"], cfg["init_hi"], cfg["init_seed"])
-    from parity import step_both
     for s in st:
         step_both(o, g, cfg, s, torch)
     compare_state(o, g, cfg)
+
+
+# Calls past 2M lookups of the general route, whose kernels of large steps (k_update and
+# k_partials not spread) the industrial and stress workloads run in one configuration each.
+LARGE_STEPS = {
+    "lfu_d64": dict(rows=[30_000, 500, 30_001], dim=64, bits=8, policy="lfu", lfu_decay_interval=2, assoc=4, batch=38_000,
+                    optimizer="adagrad", rounding="stochastic"),
+    "direct_fp16_d128": dict(rows=[60_000], dim=128, bits=16, policy="lru", assoc=1, batch=110_000, rounding="stochastic"),
+    "no_cache_d16": dict(rows=[50_000, 900], dim=16, bits=2, cache_fraction=0.0, batch=60_000),
+    "assoc64_int8_d32": dict(rows=[20_000, 77, 9000], dim=32, bits=8, policy="lru", assoc=64, batch=37_001,
+                             optimizer="adagrad"),
+}
+
+
+@pytest.mark.parametrize("case", list(LARGE_STEPS))
+def test_general_steps_past_2m_lookups(torch, case):
+    kw = dict(dict(cache_fraction=0.05), **LARGE_STEPS[case])
+    cfg = configs.get("tiny", pooling=("uniform", 0, 40), zipf=1.2, **kw)
+    o, g = make_pair(cfg, max_indices=2_600_000)
+    for k in range(3):
+        st = workload.make_step(cfg, k)
+        if k == 1:
+            st["indices"][::997] = -1
+        assert route(cfg, st["indices"].size) == "general" and st["indices"].size > 1 << 21
+        log(f"general step {case}: {st['indices'].size} lookups")
+        step_both(o, g, cfg, st, torch)
+        compare_state(o, g, cfg)

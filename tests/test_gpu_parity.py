@@ -5,6 +5,7 @@ import pytest
 
 from common import custom_cfg, oracle_from_cfg
 from parity import assert_f32, assert_same, compare_state, log, make_pair, step_both, to_dev
+from route import route
 from paper_2010_11305_amd import configs, workload
 
 pytestmark = pytest.mark.gpu
@@ -113,6 +114,18 @@ STEP_CASES = {
     "seg_tables_small": {"rows": [200, 250, 17, 240, 1, 199] * 60, "batch": 40, "assoc": 2, "cache_fraction": 0.05,
                          "pooling": ("uniform", 0, 5)},
 }
+# Calls of up to 512 tables and 2M lookups take shorter routes (embc_route.h).  With 9-row tables
+# behind the case's own, 513 in all, the general route's whole-key sort and per-table sort run.
+GENERAL_TABLES = 513
+
+
+def general(kw):
+    return dict(kw, rows=kw["rows"] + [9] * (GENERAL_TABLES - len(kw["rows"])))
+
+
+for _name in ("multi_table", "seg_tables", "seg_tables_lfu_sr_adagrad", "seg_tables_small", "big_rows_d64_lfu_sr"):
+    STEP_CASES[_name + "_general"] = general(STEP_CASES[_name])
+STEP_CASES["seg_tables_direct_general"] = dict(STEP_CASES["seg_tables_general"], assoc=1, rounding="stochastic", bits=16)
 
 
 def sort_passes(cfg):
@@ -133,8 +146,9 @@ def test_step_parity(torch, case):
     cfg = custom_cfg(**STEP_CASES[case])
     log(f"step parity {case}: rows={cfg['rows'][:4]} dim={cfg['dim']} bits={cfg['bits']} assoc={cfg['assoc']}")
     o, g = make_pair(cfg)
-    for k in range(8):
+    for k in range(3 if case.endswith("_general") else 8):
         st = workload.make_step(cfg, k)
+        assert (route(cfg, st["indices"].size) == "general") == case.endswith("_general")
         step_both(o, g, cfg, st, torch)
         compare_state(o, g, cfg)
     s = o.stats(0)
@@ -175,7 +189,8 @@ def test_wide_row_layouts(torch, dim, bits, sb16, policy):
         assert tot["hit_evictions"] > 0
 
 
-@pytest.mark.parametrize("case", ["multi_table", "seg_tables_lfu_sr_adagrad", "big_rows_d64_lfu_sr"])
+@pytest.mark.parametrize("case", ["multi_table", "seg_tables_lfu_sr_adagrad", "big_rows_d64_lfu_sr", "multi_table_general",
+                                  "seg_tables_lfu_sr_adagrad_general"])
 def test_tables_without_lookups(torch, case):
     """Steps in which some tables (first, last, in the middle, all but one) have only
     empty bags: their unique-row ranges are empty, their sort segments hold no key, and
@@ -280,21 +295,25 @@ def test_big_row_cases_have_rows_past_512_lookups():
 
 def test_seg_cases_take_the_per_table_sort():
     for case in ("seg_tables", "seg_tables_lfu_sr_adagrad", "seg_tables_small"):
-        whole, seg = sort_passes(custom_cfg(**STEP_CASES[case]))
-        assert seg < whole, case
+        for name in (case, case + "_general"):  # the shorter routes sort per table whatever the passes
+            whole, seg = sort_passes(custom_cfg(**STEP_CASES[name]))
+            assert seg < whole, name
+    whole, seg = sort_passes(custom_cfg(**STEP_CASES["multi_table_general"]))
+    assert seg == whole
     whole, seg = sort_passes(configs.get("industrial"))
     assert (whole, seg) == (4, 3)
 
 
-def test_per_table_sort_with_skipped_lookups(torch):
+@pytest.mark.parametrize("case", ["seg_tables", "seg_tables_general"])
+def test_per_table_sort_with_skipped_lookups(torch, case):
     """Per-table sort with skipped lookups inside bags (negative and out-of-range rows),
     positions before the first and after the last bag, and tables without lookups."""
     from paper_2010_11305_amd.emb_cache import EMB_EINDEX
-    cfg = custom_cfg(**dict(STEP_CASES["seg_tables"], batch=64))
+    cfg = custom_cfg(**dict(STEP_CASES[case], batch=64 if case == "seg_tables" else 16))
     assert sort_passes(cfg)[1] < sort_passes(cfg)[0]
     rng = np.random.default_rng(11)
     T, B = len(cfg["rows"]), cfg["batch"]
-    o, g = make_pair(cfg, max_indices=8192)
+    o, g = make_pair(cfg, max_indices=80_000)
     for k in range(4):
         idx, off = [int(v) for v in rng.integers(-3, 10, size=3)], [3]
         for t in range(T):
@@ -309,6 +328,7 @@ def test_per_table_sort_with_skipped_lookups(torch):
         idx += [5, -1]
         st = {"indices": np.array(idx, dtype=np.int32), "offsets": np.array(off, dtype=np.int32), "batch": B,
               "grad": rng.standard_normal((B, T, cfg["dim"])).astype(np.float32)}
+        assert (route(cfg, len(idx)) == "general") == (case == "seg_tables_general")
         log(f"per-table sort with skipped lookups: step {k}, {len(idx)} positions")
         step_both(o, g, cfg, st, torch)
         compare_state(o, g, cfg)
@@ -345,16 +365,19 @@ def test_malformed_offsets_skip_the_step(torch):
     assert np.array_equal(before["codes"], after["codes"]) and g.stats(0)["unique"] == 0
 
 
-def test_malformed_offsets_per_table_sort(torch):
-    """Malformed offsets with the per-table sort (every key skipped, the stream one
-    segment): no fault, the flag set, no state change; the next good step matches the oracle."""
+@pytest.mark.parametrize("case", ["seg_tables", "seg_tables_general", "multi_table_general"])
+def test_malformed_offsets_per_table_sort(torch, case):
+    """Malformed offsets with the per-table sort (on the general route every key is skipped and the
+    stream is one segment) and with the whole-key sort: no fault, the flag set, no state
+    change; the next good step matches the oracle."""
     from paper_2010_11305_amd.emb_cache import EMB_EINDEX, EMB_OK
-    cfg = custom_cfg(**dict(STEP_CASES["seg_tables"], batch=64))
-    assert sort_passes(cfg)[1] < sort_passes(cfg)[0]
+    cfg = custom_cfg(**dict(STEP_CASES[case], batch=64 if case == "seg_tables" else 16))
+    assert (sort_passes(cfg)[1] < sort_passes(cfg)[0]) == case.startswith("seg")
     T, B = len(cfg["rows"]), cfg["batch"]
-    log("malformed offsets, per-table sort")
-    o, g = make_pair(cfg, max_indices=20000)
+    log(f"malformed offsets, {case}")
+    o, g = make_pair(cfg, max_indices=120_000)
     st = workload.make_step(cfg, 0)
+    assert (route(cfg, st["indices"].size) == "general") == case.endswith("_general")
     before = [g.export_rows(t) for t in range(T)]
     off = st["offsets"].copy()
     off[T * B // 2] = off[-1] + 5   # past the end
@@ -372,15 +395,17 @@ def test_malformed_offsets_per_table_sort(torch):
     assert g.check() == EMB_OK
 
 
-def test_malformed_offsets_on_a_decay_step(torch):
+@pytest.mark.parametrize("tables", [1, GENERAL_TABLES])
+def test_malformed_offsets_on_a_decay_step(torch, tables):
     """LFU with counts halved every 2 steps: the call of step 2 (a decay step) has
     malformed offsets.  It is rejected on both sides without halving the counts, both
     count the step, and the next steps (3 without decay, 4 with) match the oracle."""
     from paper_2010_11305_amd.emb_cache import EMB_EINDEX, EMB_OK
-    cfg = custom_cfg(policy="lfu", lfu_decay_interval=2, assoc=4, rounding="stochastic")
+    cfg = custom_cfg(rows=[1000] + [9] * (tables - 1), policy="lfu", lfu_decay_interval=2, assoc=4, rounding="stochastic")
     B = cfg["batch"]
-    log("malformed offsets on an LFU decay step")
+    log(f"malformed offsets on an LFU decay step, {tables} tables")
     o, g = make_pair(cfg)
+    assert (route(cfg, workload.make_indices(cfg, 2)[0].size) == "general") == (tables > 512)
     for k in range(2):
         step_both(o, g, cfg, workload.make_step(cfg, k), torch)
     counts = g.export_rows(0)["cnt"].copy()
@@ -401,16 +426,16 @@ def test_malformed_offsets_on_a_decay_step(torch):
     assert g.check() == EMB_OK
 
 
-@pytest.mark.parametrize("case", ["tiny", "seg_tables"])
+@pytest.mark.parametrize("case", ["tiny", "seg_tables", "seg_tables_general", "multi_table_general"])
 def test_empty_steps(torch, case):
     """A step without bags (B = 0) and a step whose bags are all empty (no lookups): no
     fault, no error, pooled outputs +0, no state change; the oracle agrees on both, and
     a full step afterwards still matches it."""
     from paper_2010_11305_amd.emb_cache import EMB_OK
-    cfg = custom_cfg(**dict(STEP_CASES.get(case, {}), batch=32))
+    cfg = custom_cfg(**dict(STEP_CASES.get(case, {}), batch=32 if not case.endswith("_general") else 8))
     T, B, d = len(cfg["rows"]), cfg["batch"], cfg["dim"]
     log(f"empty steps {case}")
-    o, g = make_pair(cfg, max_indices=30000)
+    o, g = make_pair(cfg, max_indices=70_000)
     step_both(o, g, cfg, workload.make_step(cfg, 0), torch)
     before = [g.export_rows(t) for t in range(T)]
     # no bags at all

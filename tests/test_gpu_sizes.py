@@ -155,6 +155,10 @@ def test_mid_step(torch, case):
     """Calls past the small limits, with invalid indices in the second step."""
     cfg = custom_cfg(**MID[case])
     log(f"mid step {case}")
+    L = workload.make_indices(cfg, 0)[0].size
+    assert route(cfg, L) == ("general" if case == "many_tables" else "mid")
+    if case.startswith("forward"):
+        assert one_kernel_forward(cfg, L) == (case == "forward_below")
 
     def edit(st, k):
         if k == 1:
@@ -178,6 +182,7 @@ def test_general_step(torch, dim, knobs):
             st["indices"][::997] = -1
 
     idx, off = workload.make_indices(cfg, 0)
+    assert route(cfg, idx.size) == "general"
     assert max(np.bincount(idx[off[t * 64]:off[(t + 1) * 64]]).max() for t in range(1, 5)) > 512
     steps(torch, cfg, 2, edit)
 
