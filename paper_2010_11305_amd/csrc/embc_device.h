@@ -672,4 +672,17 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
   return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
 
+// Lanes whose 8-bit digits are equal, among the `valid` lanes of the wave.
+__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid) {
+  uint64_t m = __ballot(valid);
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    // keep the lanes whose bit b equals this lane's: bit b sign-extended, XNOR the ballot
+    const uint32_t s = (uint32_t)((int32_t)(d << (31 - b)) >> 31);
+    const uint64_t bb = __ballot(s != 0);
+    m &= ~(bb ^ (((uint64_t)s << 32) | s));
+  }
+  return m;
+}
+
 }  // namespace embc

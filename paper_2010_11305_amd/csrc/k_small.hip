@@ -57,18 +57,6 @@ __device__ __forceinline__ T front_scan_exclusive(T v, T zero, T* lds, T& total,
   return op(pre, e);
 }
 
-// Lanes whose 8-bit digits are equal, among the `valid` lanes of the wave.
-__device__ __forceinline__ uint64_t same_digit(uint32_t d, bool valid) {
-  uint64_t m = __ballot(valid);
-#pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const uint32_t s = (uint32_t)((int32_t)(d << (31 - b)) >> 31);
-    const uint64_t bb = __ballot(s != 0);
-    m &= ~(bb ^ (((uint64_t)s << 32) | s));
-  }
-  return m;
-}
-
 struct FrontLds {
   uint32_t key[kFrontTile];
   uint32_t val[kFrontTile];
@@ -93,7 +81,7 @@ __device__ __forceinline__ void front_rank(FrontLds& S, const uint32_t (&k)[ITEM
   for (int i = 0; i < ITEMS; ++i) {
     const bool valid = (uint32_t)(wv * 64 * ITEMS + i * 64 + lane) < n;
     const uint32_t d = (k[i] >> shift) & 255u;
-    const uint64_t peers = same_digit(d, valid);
+    const uint64_t peers = match_digit(d, valid);
     const uint32_t before = (uint32_t)__popcll(peers & lanemask_lt());
     uint32_t old = 0;
     if (valid && before == 0) old = atomicAdd(&S.cnt[wv][d], (uint32_t)__popcll(peers));
@@ -830,60 +818,60 @@ __device__ __forceinline__ void decide_sets(const Dev& dv, const Work& w, TabPre
         H += (uint32_t)__popcll(__ballot(hit) & gmask);
       }
     } else {
-    uint4 next = w.umeta[min(u0 + l, u1 - 1)], next2 = w.umeta[min(u0 + G + l, u1 - 1)];
-    int32_t cnext = !lru ? dv.cnt[next.x] : 0;
-    for (uint32_t c = u0; c < u1; c += G) {
-      const uint32_t u = c + l;
-      const bool act = u < u1;
-      const uint4 meta = next;
-      const int32_t cnt0 = cnext;
-      next = next2;
-      next2 = w.umeta[min(u + 2 * G, u1 - 1)];
-      if (!lru && c + G < u1) cnext = dv.cnt[next.x];
-      const int32_t r = (int32_t)(meta.x - (uint32_t)td.row_base);
-      int way = -1;
-      if (A >= 4) {
-        for (int j = 0; j < A; j += 4) {
-          const int4 tj = *reinterpret_cast<const int4*>(tags + gb + j);
-          // (the last way that holds the row, as probe_set: an imported cache may hold it twice)
-          way = tj.w == r ? j + 3 : tj.z == r ? j + 2 : tj.y == r ? j + 1 : tj.x == r ? j : way;
-        }
-      } else {
-        for (int j = 0; j < A; ++j) way = tags[gb + j] == r ? j : way;
-      }
-      const bool hit = act && way >= 0, miss = act && way < 0;
-      if (act) {
-        w.uact[u] = hit ? kActHitStay : kActBypass;
-        w.uslot[u] = hit ? (int32_t)(sbase + way) : -1;
-        int32_t cn = 0;
-        if (lru) {
-          if (hit) dv.ts[sbase + way] = (int32_t)step;
+      uint4 next = w.umeta[min(u0 + l, u1 - 1)], next2 = w.umeta[min(u0 + G + l, u1 - 1)];
+      int32_t cnext = !lru ? dv.cnt[next.x] : 0;
+      for (uint32_t c = u0; c < u1; c += G) {
+        const uint32_t u = c + l;
+        const bool act = u < u1;
+        const uint4 meta = next;
+        const int32_t cnt0 = cnext;
+        next = next2;
+        next2 = w.umeta[min(u + 2 * G, u1 - 1)];
+        if (!lru && c + G < u1) cnext = dv.cnt[next.x];
+        const int32_t r = (int32_t)(meta.x - (uint32_t)td.row_base);
+        int way = -1;
+        if (A >= 4) {
+          for (int j = 0; j < A; j += 4) {
+            const int4 tj = *reinterpret_cast<const int4*>(tags + gb + j);
+            // (the last way that holds the row, as probe_set: an imported cache may hold it twice)
+            way = tj.w == r ? j + 3 : tj.z == r ? j + 2 : tj.y == r ? j + 1 : tj.x == r ? j : way;
+          }
         } else {
-          const int64_t cc = (int64_t)cnt0 + meta.w;
-          cn = cc > 0x7FFFFFFF ? 0x7FFFFFFF : (int32_t)cc;
-          dv.cnt[meta.x] = cn;
-          const unsigned long long key = hit ? 0ull : ((unsigned long long)(uint32_t)cn << 32) | (uint32_t)~meta.x;
-          keep(key, (int32_t)u);
-          if (u1 - u0 > 4 * (uint32_t)G) w.ukey[u] = key;
+          for (int j = 0; j < A; ++j) way = tags[gb + j] == r ? j : way;
         }
-        if (hit) {
-          L.hitu[gb + way] = (int32_t)u;
-          hitc[gb + way] = cn;
+        const bool hit = act && way >= 0, miss = act && way < 0;
+        if (act) {
+          w.uact[u] = hit ? kActHitStay : kActBypass;
+          w.uslot[u] = hit ? (int32_t)(sbase + way) : -1;
+          int32_t cn = 0;
+          if (lru) {
+            if (hit) dv.ts[sbase + way] = (int32_t)step;
+          } else {
+            const int64_t cc = (int64_t)cnt0 + meta.w;
+            cn = cc > 0x7FFFFFFF ? 0x7FFFFFFF : (int32_t)cc;
+            dv.cnt[meta.x] = cn;
+            const unsigned long long key = hit ? 0ull : ((unsigned long long)(uint32_t)cn << 32) | (uint32_t)~meta.x;
+            keep(key, (int32_t)u);
+            if (u1 - u0 > 4 * (uint32_t)G) w.ukey[u] = key;
+          }
+          if (hit) {
+            L.hitu[gb + way] = (int32_t)u;
+            hitc[gb + way] = cn;
+          }
         }
+        const uint64_t mm = __ballot(miss) & gmask;
+        if (lru) {
+          // the candidates: the first missed rows in row order
+          const uint32_t rank = M + (uint32_t)__popcll(mm & below);
+          if (miss && rank < (uint32_t)A) {
+            L.cand_u[gb + rank] = (int32_t)u;
+            L.cand_pv[gb + rank] = (long long)step;
+          }
+          if (mm) last_miss = (int64_t)c + (63 - __clzll((unsigned long long)mm)) - gb;
+        }
+        M += (uint32_t)__popcll(mm);
+        H += (uint32_t)__popcll(__ballot(hit) & gmask);
       }
-      const uint64_t mm = __ballot(miss) & gmask;
-      if (lru) {
-        // the candidates: the first missed rows in row order
-        const uint32_t rank = M + (uint32_t)__popcll(mm & below);
-        if (miss && rank < (uint32_t)A) {
-          L.cand_u[gb + rank] = (int32_t)u;
-          L.cand_pv[gb + rank] = (long long)step;
-        }
-        if (mm) last_miss = (int64_t)c + (63 - __clzll((unsigned long long)mm)) - gb;
-      }
-      M += (uint32_t)__popcll(mm);
-      H += (uint32_t)__popcll(__ballot(hit) & gmask);
-    }
     }
     __builtin_amdgcn_wave_barrier();
     if (l == 0) ps.hits += H;

@@ -249,19 +249,6 @@ template hipError_t scan_exclusive<unsigned long long>(const unsigned long long*
                                                        unsigned long long*, hipStream_t);
 
 // ---- LSD radix sort of (key, value) pairs -----------------------------------------------
-// Lanes whose 8-bit digits are equal, among the `valid` lanes of the wave.
-__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid) {
-  uint64_t m = __ballot(valid);
-#pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    // keep the lanes whose bit b equals this lane's: bit b sign-extended, XNOR the ballot
-    const uint32_t s = (uint32_t)((int32_t)(d << (31 - b)) >> 31);
-    const uint64_t bb = __ballot(s != 0);
-    m &= ~(bb ^ (((uint64_t)s << 32) | s));
-  }
-  return m;
-}
-
 // Stable LSD radix sort, one kernel per 8-bit digit pass, after the Onesweep method
 // (Adinets and Merrill, "Onesweep: A Faster Least Significant Digit Radix Sort for
 // GPUs", 2022): one histogram pass for every digit, then per digit pass a single
