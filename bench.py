@@ -29,7 +29,8 @@ METRIC = "pooled lookups/sec + achieved HBM GB/s (fwd+bwd+update), 1 MI355X"
 HBM_PEAK_GBS = 8000.0
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "industrial_step_hbm_counters.md")
 # sources that determine the row-update kernel's code (its HBM counters go stale when they change)
-UPDATE_KERNEL_SOURCES = ["k_update.hip", "embc_row.h", "embc_device.h", "embc_internal.h", "embc_dispatch.h", "embc_sort.h"]
+UPDATE_KERNEL_SOURCES = ["k_update.hip", "embc_row.h", "embc_device.h", "embc_internal.h", "embc_route.h", "embc_dispatch.h",
+                         "embc_sort.h"]
 
 
 def update_kernel_digest():
