@@ -9,23 +9,32 @@ namespace embc {
 // Small calls (k_small.hip): three launches, in which one workgroup per table sorts the table's
 // lookups.  Measured steps (us), small against mid path and against the general one: 26
 // tables of 2048 lookups 44, 84 and 211, 16 of 4000: 52, 91 and 174, one of 8000: 57, 83 and
-// 154.  Past 8192 lookups in a table its workgroup sorts in memory, and the host, which knows
-// the number of lookups of all tables together, cannot see that: with nearly all of them in
-// one of 8 tables, 12000 lookups take 105 us here, 86 and 150 there, 20000: 152, 94 and 157,
-// 65536: 374, 116 and 188 (one of 100 tables 377, 166 and 262), and 17000 of 2000 rows alone 161,
-// 83 and 149.  So the line is drawn at 8192 per table on average, and in all where one table
-// could hold them (12288 and 64 more per table: the general path's launches grow with the
-// tables), but at 65536 where the lookups are a multiple of a thousand bags or more: then the
-// bags have one length, and the tables one number of lookups (or, once in as many calls as
-// there are bags, they do not).
+// 154, 26 of 800 ragged ones 34, 74 and 184, 8 of 3000: 46, 83 and 156.  Past 8192 lookups in a
+// table its workgroup sorts in memory, and the host, which knows the number of lookups of all
+// tables together, cannot see that: with nearly all of them in one of 8 tables, 16384 take
+// 116 us here, 90 and 150 there, 24576: 162, 97 and 151, 65536: 374, 116 and 188; in one of 26
+// tables, 24576: 164, 99 and 179, 32768: 208, 103 and 186; in one of 100, 32768: 210, 128 and 238,
+// 45000: 290, 145 and 257.  So the line is drawn at 8192 per table on average, and in all where
+// one table with all of them would be about as long here as on the general path (20480 and 120
+// more per table: the general path's launches grow with the tables).  Calls beyond it whose
+// tables hold as many lookups each lose by it (26 tables, 32768 lookups: 39 here, 78 there), but
+// less than those of one long feature would on this side.  The line is 65536 where the lookups
+// are a multiple of 64 bags or more: then the bags have one length, and the tables one
+// number of lookups (or, once in as many calls as there are bags, they do not).
 // A set is decided by one group of lanes, row by row: 8000 rows of one set take 139 us, 88 and
-// 160; 17000 of 2048 rows 204, 96 and 157.  Past 8192 uneven lookups in all, tables with that
-// many rows per set (set_rows: of the table with the most) go to the mid path.
+// 160; 12800 of one 420, 156 and 231 (one-lookup rows), of 2048 rows 191, 99 and 167; but 21440 of 16 sets
+// of 3200 rows 173, 101 and 179.  Past 8192 uneven lookups in all, tables with that many rows in
+// fewer than 8 sets (set_rows: of the table with the most) go to the mid path.
 constexpr int64_t kSmallLookups = 65536;
 constexpr int64_t kSmallPerTable = 8192;
-constexpr int64_t kSmallUneven = 12288, kSmallUnevenPerTable = 64, kSmallEvenBags = 1024, kSmallSetRows = 1024;
+constexpr int64_t kSmallUneven = 20480, kSmallUnevenPerTable = 120, kSmallEvenBags = 64, kSmallSetRows = 1024;
+constexpr int64_t kSmallFewSets = 8;
 constexpr int kSmallTables = 512;
 constexpr int32_t kSmallBags = 65536;
+// Rows per set of a table, as far as small_call asks for them.
+constexpr int64_t small_set_rows(int64_t n_sets, int64_t rows_per_set) {
+  return n_sets > 0 && n_sets < kSmallFewSets ? rows_per_set : 0;
+}
 constexpr bool small_call(int64_t L, int32_t B, int T, int64_t set_rows) {
   if (L > kSmallLookups || L > kSmallPerTable * T || B > kSmallBags || T > kSmallTables) return false;
   if (L <= kSmallPerTable) return true;

@@ -245,7 +245,7 @@ struct emb_cache {
   uint64_t step = 0;
   int key_bits = 1;
   int local_passes = 1;  // digit passes of the largest table's local keys
-  int64_t set_rows = 0;  // most rows that share a set
+  int64_t set_rows = 0;  // most rows that share one of few sets (small_set_rows)
   int seg_passes = 0;  // digit passes of the per-table sort, 0 = sort the whole key
   // measurement: event pairs around the row-update kernel of the last kTimedCalls calls
   static constexpr int kTimedCalls = 64;
@@ -390,7 +390,7 @@ int create_impl(const emb_cache_config* cfg, void* state, size_t state_bytes, vo
     int64_t max_range = 1;
     for (int t = 0; t < cfg->num_tables; ++t) {
       max_range = std::max(max_range, p.key_base[t + 1] - p.key_base[t]);
-      if (p.desc[t].n_sets > 0) h->set_rows = std::max(h->set_rows, p.desc[t].Q);
+      h->set_rows = std::max(h->set_rows, embc::small_set_rows(p.desc[t].n_sets, p.desc[t].Q));
     }
     const int seg = (bit_length((uint64_t)max_range) + 7) / 8;
     h->local_passes = seg;

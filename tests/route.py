@@ -15,6 +15,7 @@ SOURCE = """
 extern "C" int route(int64_t L, int32_t B, int T, int dim, int64_t set_rows) {
   return embc::small_call(L, B, T, set_rows) ? 0 : embc::mid_call(L, B, T, dim) ? 1 : 2;
 }
+extern "C" int64_t set_rows(int64_t n_sets, int64_t rows) { return embc::small_set_rows(n_sets, rows); }
 extern "C" int fused(int64_t L, int64_t nbags, int dim, int assoc) { return embc::fused_call(L, nbags, dim, assoc); }
 """
 
@@ -26,13 +27,18 @@ def _lib():
         with open(src, "w") as f:
             f.write(SOURCE)
         subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", f"-I{CSRC}", src, "-o", so], check=True)
-        return ctypes.CDLL(so)
+        lib = ctypes.CDLL(so)
+        lib.set_rows.restype = ctypes.c_int64
+        return lib
 
 
 def set_rows(cfg):
-    """The most rows of a table that share a set (0 without a cache)."""
+    """The most rows of a table that share one of few sets (0 without a cache)."""
     frac, assoc = cfg.get("cache_fraction", 0.0), cfg.get("assoc", 1)
-    return max(-(-n // max(1, int(np.floor(frac * n)) // assoc)) for n in cfg["rows"]) if frac > 0 else 0
+    if frac <= 0:
+        return 0
+    sets = [(max(1, int(np.floor(frac * n)) // assoc), n) for n in cfg["rows"]]
+    return max(_lib().set_rows(ctypes.c_int64(s), ctypes.c_int64(-(-n // s))) for s, n in sets)
 
 
 def route(cfg, lookups, batch=None):

@@ -349,6 +349,10 @@ LARGE = {
     "one_bag": (dict(rows=[50_000, 50, 7], batch=1, cache_fraction=0.02, **LRU), [12_288, 8, 100], 1.2),
     "two_large": (dict(rows=[50_000, 60_000] + [40] * 98, dim=64, batch=300, cache_fraction=0.02, **LRU),
                   [8200, 8300] + [9] * 98, 1.2),
+    "uneven_line": (dict(rows=[90_000] + [30] * 7, batch=100, cache_fraction=0.02, assoc=4, policy="lfu", bits=8),
+                    [21_380] + [8] * 7, 1.2),
+    "seven_sets": (dict(rows=[7168, 30, 9], batch=410, cache_fraction=0.0157, assoc=16, policy="lru", bits=8),
+                   [20_000, 10, 9], 1.02),
     "five_tiles": (dict(rows=[9] * 511 + [50_000], batch=60, cache_fraction=0.02, **LRU), [3] * 511 + [43_000], 1.2),
 }
 

@@ -25,24 +25,29 @@ def test_route_by_size(T, dim, lookups, want):
 
 @pytest.mark.parametrize("T,batch,lookups,want", [
     # past 8192 lookups a table may hold more than its workgroup's LDS
-    (2, 64, 12_416, "small"), (2, 64, 12_417, "mid"), (8, 100, 12_800, "small"), (8, 100, 12_801, "mid"),
-    (100, 50, 18_688, "small"), (100, 50, 18_689, "mid"), (512, 50, 45_056, "small"), (512, 50, 45_057, "mid"),
+    (2, 50, 16_384, "small"), (2, 50, 16_385, "mid"), (8, 100, 21_440, "small"), (8, 100, 21_441, "mid"),
+    (100, 50, 32_480, "small"), (100, 50, 32_481, "mid"), (512, 50, 65_536, "small"), (512, 50, 65_537, "mid"),
     # but not where all bags have one length
     (26, 2048, 26 * 2048, "small"), (26, 2048, 26 * 2048 + 1, "mid"), (26, 2048, 26 * 2048 - 1, "mid"),
-    (16, 100, 16 * 100 * 20, "small"), (8, 128, 65_536, "small"), (8, 127, 8 * 127 * 64, "mid"), (26, 2521, 26 * 2521, "mid"),
+    (16, 100, 16 * 100 * 20, "small"), (8, 128, 65_536, "small"), (8, 8, 64_000, "small"), (9, 7, 63_000, "mid"),
+    (26, 2521, 26 * 2521, "mid"),
     (1, 8192, 8192, "small"), (8, 70_000, 100, "mid"),
 ])
 def test_small_calls(T, batch, lookups, want):
     assert route(cfg(T, 16, batch), lookups) == want
 
 
-@pytest.mark.parametrize("frac,assoc,rows,lookups,want", [
-    (1e-6, 16, 1024, 12_000, "small"), (1e-6, 16, 1025, 12_000, "mid"), (1e-6, 16, 10**6, 8192, "small"),
-    (0.02, 16, 10**7, 12_000, "small"), (0.01, 16, 10**7, 12_000, "mid"), (0.0, 16, 10**7, 12_000, "small"),
-    (0.001, 16, 10**7, 12_000, "mid"), (0.001, 16, 10**7, 12_300, "small"), (1e-6, 16, 10**6, 8400, "small"),
+@pytest.mark.parametrize("frac,rows,lookups,want", [
+    # one set (16 ways)
+    (1e-6, 1024, 12_000, "small"), (1e-6, 1025, 12_000, "mid"), (1e-6, 10**6, 8192, "small"), (1e-6, 10**6, 8193, "mid"),
+    (1e-6, 10**6, 8610, "small"),
+    # seven sets, eight, many, none
+    (0.0157, 7168, 12_000, "small"), (0.0157, 7175, 12_000, "mid"), (0.0157, 8200, 12_000, "small"),
+    (0.001, 10**7, 20_000, "small"), (0.0, 10**7, 12_000, "small"),
 ])
-def test_small_calls_by_rows_per_set(frac, assoc, rows, lookups, want):
-    assert route({"rows": [500, rows, 40], "dim": 16, "batch": 350 if lookups % 1050 == 0 else 410, "cache_fraction": frac, "assoc": assoc}, lookups) == want
+def test_small_calls_by_rows_per_set(frac, rows, lookups, want):
+    """Three tables of 410 bags: 8610 lookups are 7 per bag."""
+    assert route({"rows": [500, rows, 40], "dim": 16, "batch": 410, "cache_fraction": frac, "assoc": 16}, lookups) == want
 
 
 def test_calls_without_bags_or_lookups():
