@@ -164,10 +164,11 @@ struct FrontTab {
   int32_t B;
   int64_t L;
   uint32_t P0, n;
+  bool bad;  // a boundary of the tables that this thread has looked at is bad
 };
 
 // The keys (k) and bags (v) of the tile of m <= 1024*ITEMS lookups from t0 on, in wave-major
-// order; true if an offset is bad.  A bag that starts in the tile marks its first position
+// order; true if an offset is bad, or a table's boundary.  A bag that starts in the tile marks its first position
 // with its number + 1 (bags without lookups mark none), and a position takes the last mark
 // at or before it: by ballot inside a run of 64, then from the run before, then from the
 // waves before.  `carry` is the mark before the tile, and is moved past it.  Bags
@@ -186,7 +187,7 @@ __device__ __forceinline__ bool front_expand(FrontLds& S, const FrontTab& f, con
   }
   for (uint32_t i = tid; i < m; i += kFrontThreads) S.val[i] = 0;
   __syncthreads();
-  bool bad = false;
+  bool bad = f.bad;
   for (int bt = b0 + tid; bt < b1; bt += 4 * kFrontThreads) {
     int32_t x[4], y[4];
 #pragma unroll
@@ -378,7 +379,7 @@ __device__ __forceinline__ bool front_large(FrontLds& S, const Work& w, const Fr
   uint32_t* k0 = (passes & 1) ? ka : kb;
   uint32_t* v0 = (passes & 1) ? va : vb;
   uint32_t carry = 0;
-  bool bad = false;  // every offset is checked before the tiles look for theirs
+  bool bad = f.bad;  // every offset is checked before the tiles look for theirs
   for (int b0 = threadIdx.x; b0 < f.B; b0 += 8 * kFrontThreads) {
     int32_t x[8];
 #pragma unroll
@@ -453,11 +454,12 @@ __global__ __launch_bounds__(kFrontThreads) void k_front(Dev dv, Work w, const i
   }
   const int32_t* offt = off + (int64_t)t * B;
   const int64_t p0 = B > 0 ? offt[0] : 0, p1 = B > 0 ? offt[B] : 0;
-  // every workgroup looks at all tables' boundaries before it writes: its positions are then its
-  // own (its bags inside them are checked as they are expanded)
-  bool bad = __syncthreads_or(B > 0 && bad_boundaries(off, dv.T, B, L, tid, kFrontThreads)) != 0;
+  bool bad = bad_range(p0, p1, L);  // whole workgroup, as below
   const uint32_t P0 = bad ? 0u : (uint32_t)p0, n = bad ? 0u : (uint32_t)(p1 - p0);
-  const FrontTab f{idx + P0, offt, B, L, P0, n};
+  // every workgroup looks at all tables' boundaries before it writes: its positions are then its
+  // own.  The threads learn of each other's boundaries with the bags', which are checked as
+  // they are expanded (with a barrier of its own for the check the kernel was 0.3 us longer).
+  const FrontTab f{idx + P0, offt, B, L, P0, n, B > 0 && bad_boundaries(off, dv.T, B, L, tid, kFrontThreads)};
   if (tid == 0) S.n_bad = S.n_chunk = S.n_big = S.n_window = 0;
   // expanded, sorted by the local key (a skipped lookup's digits are all 255, above every
   // valid key's, so skipped lookups end the table's run), unique rows and sets listed
